@@ -344,9 +344,7 @@ __device__ inline double cell_rate(const double *u, const RecR &rr, const RecT &
 {
     double w[8];
     cons_to_prim(u, w, gs);
-    return (fabs(w[1]) + fast_speed<0>(w, gs)) * rr.icfl
-         + (fabs(w[2]) + fast_speed<1>(w, gs)) * rr.irc * tt.icfl
-         + (fabs(w[3]) + fast_speed<2>(w, gs)) * rr.irc * tt.isinc * pp.iw;
+    return cell_rate_of(w, rr.icfl, rr.irc * tt.icfl, rr.irc * tt.isinc * pp.iw, gs);
 }
 
 // Reflux correction of one coarse cell (loc, block coordinates) behind the
@@ -549,7 +547,8 @@ __global__ void __launch_bounds__(NT) k_hancock(KArgs a)
                 double wm[NV], wp[NV], lo[NV], hi[NV], fl[NV], fh[NV];
                 prim_at<S>(a, slot, nb, i - 1, j, k, wm);
                 prim_at<S>(a, slot, nb, i + 1, j, k, wp);
-                reconstruct<LIM, NV>(wm, w0, wp, rr.idm, rr.idp, rr.idc, rr.hm, rr.hp, lo, hi);
+                reconstruct<LIM, NV>(wm, w0, wp, slope_scale<LIM>(rr.idm), slope_scale<LIM>(rr.idp), rr.idc,
+                                     rr.hm, rr.hp, lo, hi);
                 phys_flux<0, NV>(lo, fl, gs);
                 phys_flux<0, NV>(hi, fh, gs);
 #pragma unroll
@@ -559,7 +558,8 @@ __global__ void __launch_bounds__(NT) k_hancock(KArgs a)
                 double wm[NV], wp[NV], lo[NV], hi[NV], fl[NV], fh[NV];
                 prim_at<S>(a, slot, nb, i, j - 1, k, wm);
                 prim_at<S>(a, slot, nb, i, j + 1, k, wp);
-                reconstruct<LIM, NV>(wm, w0, wp, tt.idm, tt.idp, tt.idc, tt.hm, tt.hp, lo, hi);
+                reconstruct<LIM, NV>(wm, w0, wp, slope_scale<LIM>(tt.idm), slope_scale<LIM>(tt.idp), tt.idc,
+                                     tt.hm, tt.hp, lo, hi);
                 phys_flux<1, NV>(lo, fl, gs);
                 phys_flux<1, NV>(hi, fh, gs);
                 const double thm = rr.rt * tt.thm, thp = rr.rt * tt.thp;
@@ -570,14 +570,19 @@ __global__ void __launch_bounds__(NT) k_hancock(KArgs a)
                 double wm[NV], wp[NV], lo[NV], hi[NV], fl[NV], fh[NV];
                 prim_at<S>(a, slot, nb, i, j, k - 1, wm);
                 prim_at<S>(a, slot, nb, i, j, k + 1, wp);
-                reconstruct<LIM, NV>(wm, w0, wp, pk.idm, pk.idp, pk.idc, pk.hm, pk.hp, lo, hi);
+                reconstruct<LIM, NV>(wm, w0, wp, slope_scale<LIM>(pk.idm), slope_scale<LIM>(pk.idp), pk.idc,
+                                     pk.hm, pk.hp, lo, hi);
                 phys_flux<2, NV>(lo, fl, gs);
                 phys_flux<2, NV>(hi, fh, gs);
                 const double kf = rr.rt * tt.phf * pk.iw;
 #pragma unroll
                 for (int v = 0; v < NV; ++v) acc[v] -= kf * fh[v] - kf * fl[v];
             }
-            if (!a.cart) add_sources(w0, rr.rt, tt.ctil, rr.rc, tt.sinc, tt.cosc, a.omega, a.gm, acc);
+            if (!a.cart) {
+                const double c = a.omega * a.omega * rr.rc * tt.sinc, gg = a.gm * IC_RCP(rr.rc * rr.rc);
+                add_sources(w0, rr.rt, tt.ctil, 2.0 * a.omega * tt.sinc, 2.0 * a.omega * tt.cosc,
+                            fma(c, tt.sinc, -gg), c * tt.cosc, acc);
+            }
             double unew[NV];
 #pragma unroll
             for (int v = 0; v < NV; ++v) unew[v] = a.Ubase[cidx<S>(slot, v, i, j, k)] + adt * acc[v];

@@ -10,30 +10,32 @@
 
 #define DEV __device__ __forceinline__
 
-// Reciprocal of a > 0 (normal): the hardware estimate refined by two
-// Newton-Raphson steps x <- x + x (1 - a x); at most one ulp from 1/a.
+// Reciprocal of a > 0 (normal): the hardware estimate x (relative error below
+// 2^-22) and one step of third order, x (1 + e + e^2) with e = 1 - a x (one
+// operation less than two Newton steps); at most one ulp from 1/a.
 DEV double rcp_pos(double a)
 {
-    double x = __builtin_amdgcn_rcp(a);
-    double e = fma(-a, x, 1.0);
-    x = fma(x, e, x);
-    e = fma(-a, x, 1.0);
-    return fma(x, e, x);
+    const double x = __builtin_amdgcn_rcp(a);
+    const double e = fma(-a, x, 1.0);
+    return fma(x, fma(e, e, e), x);
 }
 
-// Square root of x >= 0 (normal or zero): the hardware reciprocal-square-root
-// estimate y, then one coupled Goldschmidt iteration on g = x y, h = y / 2 and
-// a final Newton correction of g; at most one ulp from sqrt(x).
+// Square root of x > 0 (normal): t = x y from the hardware reciprocal-square-
+// root estimate y, e = 1 - t y, and one step of third order t (1 + e/2 +
+// 3 e^2/8); at most one ulp from sqrt(x).
 DEV double sqrt_pos(double x)
 {
     const double y = __builtin_amdgcn_rsq(x);
-    double g = x * y, h = 0.5 * y;
-    const double r = fma(-g, h, 0.5);
-    g = fma(g, r, g);
-    h = fma(h, r, h);
-    const double d = fma(-g, g, x);
-    g = fma(d, h, g);
-    return x > 0.0 ? g : 0.0;
+    const double t = x * y, e = fma(-t, y, 1.0);
+    return fma(t * e, fma(0.375, e, 0.5), t);
+}
+
+// x / sqrt(q) for q > 0 (normal), the same step applied to x y.
+DEV double div_sqrt_pos(double x, double q)
+{
+    const double y = __builtin_amdgcn_rsq(q);
+    const double e = fma(-(q * y), y, 1.0), z = x * y;
+    return fma(z * e, fma(0.375, e, 0.5), z);
 }
 
 // Reciprocals and square roots of the finite-volume update use rcp_pos /
@@ -41,9 +43,11 @@ DEV double sqrt_pos(double x)
 #ifdef IC_EXACT_MATH
 #define IC_RCP(x) (1.0 / (x))
 #define IC_SQRT(x) sqrt(x)
+#define IC_DIV_SQRT(x, q) ((x) / sqrt(q))
 #else
 #define IC_RCP(x) rcp_pos(x)
 #define IC_SQRT(x) sqrt_pos(x)
+#define IC_DIV_SQRT(x, q) div_sqrt_pos(x, q)
 #endif
 
 struct Gas {
@@ -89,18 +93,27 @@ DEV void prim_to_cons(const double *w, double *u, const Gas &gs)
     if constexpr (NV > 8) u[8] = w[0] * w[8];
 }
 
-// Fast magnetosonic speed along direction D.
-template <int D>
-DEV double fast_speed(const double w[8], const Gas &gs)
+// Fast magnetosonic speed from A = g p + B^2, gp4 = 4 g p, the normal field bn
+// and twice the density: c_f^2 = (A + S) / (2 rho), S^2 = A^2 - 4 g p bn^2,
+// taken as X / sqrt(2 rho X) with X = A + S: no reciprocal of the density and
+// one square root less its guard (S is kept off zero by a value that vanishes
+// beside A; A > 0 in every physical state).
+DEV double fast_speed_of(double A, double gp4, double bn, double rho2)
 {
-    const double ir = IC_RCP(w[0]);
+    const double d = fmax(fma(-gp4, bn * bn, A * A), 1e-300);
+    const double X = A + IC_SQRT(d);
+    return IC_DIV_SQRT(X, rho2 * X);
+}
+
+// CFL rate of a cell, sum over the directions of (|v_d| + c_f,d) id (id the
+// reciprocal widths).
+DEV double cell_rate_of(const double w[8], double ir, double it, double ip, const Gas &gs)
+{
     const double b2 = w[5] * w[5] + w[6] * w[6] + w[7] * w[7];
-    const double gp = gs.g * w[4];
-    const double a = (gp + b2) * ir;
-    const double bn = w[5 + D];
-    double disc = a * a - 4.0 * gp * bn * bn * ir * ir;
-    disc = disc > 0.0 ? disc : 0.0;
-    return IC_SQRT(0.5 * (a + IC_SQRT(disc)));
+    const double A = fma(gs.g, w[4], b2), gp4 = 4.0 * gs.g * w[4], rho2 = w[0] + w[0];
+    return (fabs(w[1]) + fast_speed_of(A, gp4, w[5], rho2)) * ir
+         + (fabs(w[2]) + fast_speed_of(A, gp4, w[6], rho2)) * it
+         + (fabs(w[3]) + fast_speed_of(A, gp4, w[7], rho2)) * ip;
 }
 
 template <int NV = 8>
@@ -114,7 +127,10 @@ DEV bool unphysical(const double *w)
 }
 
 // Local Lax-Friedrichs (Rusanov) flux along D between left state wl and right
-// state wr; with the tracer, its flux rho v_n s takes the same maximum speed.
+// state wr: (F_l + F_r) / 2 - c / 2 (U_r - U_l); with the tracer, its flux
+// rho v_n s takes the same maximum speed.  The halves go into the normal
+// velocities and fields once, so that each component is one chain of fused
+// multiply-adds.
 template <int D, int NV = 8>
 DEV void rusanov(const double *wl, const double *wr, double *f, const Gas &gs)
 {
@@ -122,52 +138,37 @@ DEV void rusanov(const double *wl, const double *wr, double *f, const Gas &gs)
     const double vr2 = wr[1] * wr[1] + wr[2] * wr[2] + wr[3] * wr[3];
     const double bl2 = wl[5] * wl[5] + wl[6] * wl[6] + wl[7] * wl[7];
     const double br2 = wr[5] * wr[5] + wr[6] * wr[6] + wr[7] * wr[7];
-    const double ptl = wl[4] + 0.5 * bl2;
-    const double ptr = wr[4] + 0.5 * br2;
-    const double El = wl[4] * gs.igm1 + 0.5 * wl[0] * vl2 + 0.5 * bl2;
-    const double Er = wr[4] * gs.igm1 + 0.5 * wr[0] * vr2 + 0.5 * br2;
-    const double vnl = wl[1 + D], vnr = wr[1 + D];
-    const double bnl = wl[5 + D], bnr = wr[5 + D];
+    const double ptl = fma(0.5, bl2, wl[4]);
+    const double ptr = fma(0.5, br2, wr[4]);
+    const double El = fma(wl[4], gs.igm1, fma(0.5 * wl[0], vl2, 0.5 * bl2));
+    const double Er = fma(wr[4], gs.igm1, fma(0.5 * wr[0], vr2, 0.5 * br2));
     const double vbl = wl[1] * wl[5] + wl[2] * wl[6] + wl[3] * wl[7];
     const double vbr = wr[1] * wr[5] + wr[2] * wr[6] + wr[3] * wr[7];
-    // fast speeds
-    const double irl = IC_RCP(wl[0]), irr = IC_RCP(wr[0]);
-    const double gpl = gs.g * wl[4], gpr = gs.g * wr[4];
-    const double al = (gpl + bl2) * irl, ar = (gpr + br2) * irr;
-    double dl = al * al - 4.0 * gpl * bnl * bnl * irl * irl;
-    double dr = ar * ar - 4.0 * gpr * bnr * bnr * irr * irr;
-    dl = dl > 0.0 ? dl : 0.0;
-    dr = dr > 0.0 ? dr : 0.0;
-    const double cfl = IC_SQRT(0.5 * (al + IC_SQRT(dl)));
-    const double cfr = IC_SQRT(0.5 * (ar + IC_SQRT(dr)));
-    const double sl = fabs(vnl) + cfl, sr = fabs(vnr) + cfr;
-    const double c = sl > sr ? sl : sr;
-    const double hc = 0.5 * c;
+    // the larger of the two sides' maximum speeds, halved
+    const double g4 = 4.0 * gs.g;
+    const double sl = fabs(wl[1 + D]) + fast_speed_of(fma(gs.g, wl[4], bl2), g4 * wl[4], wl[5 + D], wl[0] + wl[0]);
+    const double sr = fabs(wr[1 + D]) + fast_speed_of(fma(gs.g, wr[4], br2), g4 * wr[4], wr[5 + D], wr[0] + wr[0]);
+    const double c = fmax(sl, sr), hc = 0.5 * c;
 
-    const double ml = wl[0] * vnl, mr = wr[0] * vnr;
-    f[0] = 0.5 * (ml + mr) - hc * (wr[0] - wl[0]);
+    const double hvl = 0.5 * wl[1 + D], hvr = 0.5 * wr[1 + D];
+    const double hbl = 0.5 * wl[5 + D], hbr = 0.5 * wr[5 + D];
+    const double hml = wl[0] * hvl, hmr = wr[0] * hvr;
+    f[0] = fma(-hc, wr[0] - wl[0], hml + hmr);
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-        double fl = ml * wl[1 + q] - bnl * wl[5 + q];
-        double fr = mr * wr[1 + q] - bnr * wr[5 + q];
-        if (q == D) {
-            fl += ptl;
-            fr += ptr;
-        }
-        f[1 + q] = 0.5 * (fl + fr) - hc * (wr[0] * wr[1 + q] - wl[0] * wl[1 + q]);
+        double s = fma(-hbr, wr[5 + q], fma(-hbl, wl[5 + q], fma(hmr, wr[1 + q], hml * wl[1 + q])));
+        if (q == D) s = fma(0.5, ptl + ptr, s);
+        f[1 + q] = q == D ? fma(-c, hmr - hml, s) : fma(-hc, fma(wr[0], wr[1 + q], -(wl[0] * wl[1 + q])), s);
     }
-    f[4] = 0.5 * ((El + ptl) * vnl - bnl * vbl + (Er + ptr) * vnr - bnr * vbr) - hc * (Er - El);
+    f[4] = fma(-hc, Er - El, fma(-hbr, vbr, fma(-hbl, vbl, fma(Er + ptr, hvr, (El + ptl) * hvl))));
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-        double fl = vnl * wl[5 + q] - bnl * wl[1 + q];
-        double fr = vnr * wr[5 + q] - bnr * wr[1 + q];
-        if (q == D) {
-            fl = 0.0;
-            fr = 0.0;
-        }
-        f[5 + q] = 0.5 * (fl + fr) - hc * (wr[5 + q] - wl[5 + q]);
+        const double d = wr[5 + q] - wl[5 + q];
+        if (q == D) f[5 + q] = -hc * d;
+        else f[5 + q] = fma(-hc, d, fma(-hbr, wr[1 + q], fma(-hbl, wl[1 + q], fma(hvr, wr[5 + q], hvl * wl[5 + q]))));
     }
-    if constexpr (NV > 8) f[8] = 0.5 * (ml * wl[8] + mr * wr[8]) - hc * (wr[0] * wr[8] - wl[0] * wl[8]);
+    if constexpr (NV > 8)
+        f[8] = fma(-hc, fma(wr[0], wr[8], -(wl[0] * wl[8])), fma(hmr, wr[8], hml * wl[8]));
 }
 
 // Physical ideal-MHD flux of a primitive state along D: rho v_n, rho v_n v -
@@ -193,72 +194,74 @@ DEV void phys_flux(const double *w, double *f, const Gas &gs)
     if constexpr (NV > 8) f[8] = m * w[8];
 }
 
-// Monotonised-central slope on a non-uniform coordinate (reciprocal spacings given).
-DEV double mc_slope(double wm, double w0, double wp, double idm, double idp, double idc)
-{
-    const double dm = (w0 - wm) * idm;
-    const double dp = (wp - w0) * idp;
-    const double dc = (wp - wm) * idc;
-    const double a = fmin(fabs(dc), 2.0 * fmin(fabs(dm), fabs(dp)));
-    return (dm * dp <= 0.0) ? 0.0 : copysign(a, dc);
-}
-
 // Limiters of the reconstruction (the paper's runs use the monotonised-central
 // "Woodward" form; its code offers others): zero where the one-sided
-// differences differ in sign or one vanishes, else LIM_MINMOD the one of
+// differences differ in sign or one vanishes, else LIM_MC the smallest of
+// 2 |dm|, |dc|, 2 |dp| with their sign, LIM_MINMOD the one-sided difference of
 // smaller magnitude, LIM_VANLEER their harmonic mean 2 dm dp / (dm + dp).
+// dm = (w0 - wm) im, dp = (wp - w0) ip, dc = (wp - wm) ic; im and ip are the
+// reciprocal spacings, twice them for LIM_MC (slope_scale).  MC and minmod are
+// clamps between 0 and the two differences: minima and maxima alone, no
+// comparison, sign copy or select.
 enum { LIM_MC = 0, LIM_MINMOD = 1, LIM_VANLEER = 2 };
 
 template <int LIM>
-DEV double limited_slope(double wm, double w0, double wp, double idm, double idp, double idc)
+DEV double slope_scale(double id) { return LIM == LIM_MC ? 2.0 * id : id; }
+
+template <int LIM>
+DEV double limited_slope(double wm, double w0, double wp, double im, double ip, double ic)
 {
-    if (LIM == LIM_MC) return mc_slope(wm, w0, wp, idm, idp, idc);
-    const double dm = (w0 - wm) * idm;
-    const double dp = (wp - w0) * idp;
-    double sl;
-    if (LIM == LIM_MINMOD) sl = fabs(dm) < fabs(dp) ? dm : dp;
-    else sl = 2.0 * dm * dp * IC_RCP(dm + dp);
-    return (dm * dp <= 0.0) ? 0.0 : sl;
+    const double dm = (w0 - wm) * im;
+    const double dp = (wp - w0) * ip;
+    if (LIM == LIM_VANLEER) {
+        const double sl = 2.0 * dm * dp * IC_RCP(dm + dp);
+        return (dm * dp <= 0.0) ? 0.0 : sl;
+    }
+    const double up = fmax(fmin(dm, dp), 0.0), dn = fmin(fmax(dm, dp), 0.0);   // one of them is zero
+    if (LIM == LIM_MINMOD) return up + dn;
+    return fmax(fmin((wp - wm) * ic, up), dn);
 }
 
 // Face values of a cell from its neighbours along one direction; falls back to
-// zero slope for all variables if a face density or pressure is not positive.
+// zero slope for all variables if a face density or pressure is not positive
+// (rare: a branch that no lane takes is skipped).
 template <int LIM = LIM_MC, int NV = 8>
-DEV void reconstruct(const double *wm, const double *w0, const double *wp, double idm,
-                     double idp, double idc, double hm, double hp, double *lo, double *hi)
+DEV void reconstruct(const double *wm, const double *w0, const double *wp, double im,
+                     double ip, double ic, double hm, double hp, double *lo, double *hi)
 {
-    double s[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) s[v] = limited_slope<LIM>(wm[v], w0[v], wp[v], idm, idp, idc);
-    // the density and pressure face values decide; a zero slope gives w0 - 0 * h = w0 exactly
-    const bool ok = w0[0] - s[0] * hm > 0.0 && w0[0] + s[0] * hp > 0.0 && w0[4] - s[4] * hm > 0.0 &&
-                    w0[4] + s[4] * hp > 0.0;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        const double sv = ok ? s[v] : 0.0;
-        lo[v] = w0[v] - sv * hm;
-        hi[v] = w0[v] + sv * hp;
+        const double s = limited_slope<LIM>(wm[v], w0[v], wp[v], im, ip, ic);
+        lo[v] = fma(-s, hm, w0[v]);
+        hi[v] = fma(s, hp, w0[v]);
     }
+    const bool ok = lo[0] > 0.0 && hi[0] > 0.0 && lo[4] > 0.0 && hi[4] > 0.0;
+    if (!ok)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) lo[v] = hi[v] = w0[v];
 }
 
 // Geometric (hoop), frame (Coriolis, centrifugal) and gravity sources of a
-// cell in spherical geometry, added to acc.
-DEV void add_sources(const double w[8], double rt, double ctil, double rc, double sc, double cc,
-                     double om, double gm, double acc[8])
+// cell in spherical geometry, added to acc.  Per cell: rt = 1/r and ctil = cot
+// theta in finite-volume form, s2 = 2 omega sin, c2 = 2 omega cos (theta), and
+// the accelerations at rest gr = omega^2 r sin^2 - G M / r^2 and gt = omega^2 r
+// sin cos.
+DEV void add_sources(const double w[8], double rt, double ctil, double s2, double c2, double gr, double gt,
+                     double acc[8])
 {
-    const double rho = w[0], vr = w[1], vt = w[2], vp = w[3];
+    const double vr = w[1], vt = w[2], vp = w[3];
     const double br = w[5], bt = w[6], bp = w[7];
-    const double ptot = w[4] + 0.5 * (br * br + bt * bt + bp * bp);
-    const double g = -gm * IC_RCP(rc * rc);
-    acc[1] += rt * (rho * (vt * vt + vp * vp) - (bt * bt + bp * bp) + 2.0 * ptot)
-              + rho * (2.0 * om * sc * vp + om * om * rc * sc * sc) + rho * g;
-    acc[2] += rt * (-(rho * vr * vt - br * bt) + ctil * (rho * vp * vp - bp * bp + ptot))
-              + rho * (2.0 * om * cc * vp + om * om * rc * sc * cc);
-    acc[3] += -rt * ((rho * vp * vr - bp * br) + ctil * (rho * vp * vt - bp * bt))
-              - 2.0 * om * rho * (sc * vr + cc * vt);
-    acc[4] += rho * vr * g + rho * om * om * rc * sc * (vr * sc + vt * cc);
+    const double mr = w[0] * vr, mt = w[0] * vt, mp = w[0] * vp;
+    const double pp = fma(mp, vp, -(bp * bp));           // rho v_p^2 - B_p^2
+    const double tt = fma(mt, vt, -(bt * bt));
+    const double ptot = fma(0.5, br * br + bt * bt + bp * bp, w[4]);
+    acc[1] += rt * (pp + tt + 2.0 * ptot) + fma(s2, mp, w[0] * gr);
+    acc[2] += rt * (ctil * (pp + ptot) - fma(mr, vt, -(br * bt))) + fma(c2, mp, w[0] * gt);
+    acc[3] -= rt * (fma(mp, vr, -(bp * br)) + ctil * fma(mp, vt, -(bp * bt))) + fma(s2, mr, c2 * mt);
+    acc[4] += fma(mr, gr, mt * gt);
+    const double rp = vp * br - bp * vr;
     acc[6] += rt * (vr * bt - vt * br);
-    acc[7] += -rt * ((vp * br - bp * vr) + ctil * (vp * bt - bp * vt));
+    acc[7] -= rt * (rp + ctil * (vp * bt - bp * vt));
 }
 
 // Small-value floors on a conserved state: density first (a cell below the

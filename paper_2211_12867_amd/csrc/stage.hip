@@ -4,22 +4,34 @@
 // Woodward-type limiter, second order): a work-group marches along k (phi)
 // through a leaf block (or through a part of it, down to one plane, for short
 // work lists).
+//
 // For each k-plane the primitives of the plane and of its two-cell i/j halos
-// sit in LDS; every cell is reconstructed once per direction, and every r- and
-// theta-face flux of the plane is computed once by one thread (which takes the
-// left state from its neighbouring lane through LDS) and kept in LDS; the
-// phi-face fluxes are computed once per column
-// in registers (each of the first 192 or fewer threads owns one (i, j) column
-// and carries the previous plane's flux, face state and the next plane's
-// primitives).  The update adds the flux differences with the finite-volume
-// metric, the hoop, Coriolis, centrifugal and gravity sources, applies the
-// floors and writes U_out = U_base + alpha dt L(U).  The last wave, which owns
-// no column, starts the asynchronous HBM-to-LDS copy of the next plane's halo
-// once its share of the plane's r/theta fluxes is done; during the update it
-// starts the copy of the column plane three ahead, waits for both and converts
-// the halo to primitives.  Halo cells come from neighbouring blocks (same
-// level), the block's own edge (outflow) or ghost slabs (inner boundary,
-// coarse-fine faces).  The block's phi metric records sit in LDS.
+// sit in LDS.  The r- and theta-faces are done in passes of one wave each: rows
+// (columns) of cells on adjacent lanes, every cell reconstructed once per
+// direction, every face flux computed once, the face state of the cell below
+// and the flux of the face above passed between lanes (DPP), and each cell's
+// flux difference added to its place in LDS.  The phi-faces and the update
+// belong to the thread of the column (i, j): flux differences with the
+// finite-volume metric, hoop, Coriolis, centrifugal and gravity sources,
+// floors, U_out = U_base + alpha dt L(U), in the second stage the CFL rate.
+// Threads without a column turn the halo cells of the next plane into
+// primitives.  Halo cells come from neighbouring blocks (same level), the
+// block's own edge (outflow) or ghost slabs (inner boundary, coarse-fine
+// faces).
+//
+// What bounds it: fp64 instructions and the latency between them.  Two
+// work-groups share a CU (256 VGPRs a lane; 77 KB of LDS on 16 x 12 planes),
+// two waves a SIMD; a fp64 operation issues every 4 cycles (at full load the
+// clock takes that to 4.3 to 5.4 of 2.4 GHz) and its result is there after 8.
+// Hence: few operations (limiters as minima and maxima, no reciprocal in the
+// fast speed), the passes spread over the four waves so that no SIMD carries
+// more than another (PassSplit), one barrier a plane (two planes of primitives
+// and of differences in LDS), loads into registers a plane ahead, LDS rows
+// pitched against bank conflicts, nothing spilled in the plane loop.
+// Measured on 512 x 60 x 180 cells (2,400 blocks of 16 x 12 x 12): 403 us a
+// launch, before 484 us; 4,096 blocks of 12^3: 543 us (13.0 G cells/s); 8 blocks
+// of 12^3, one work-group each: 52 us, before 71 us (a wave without columns did
+// nothing in the face phases of 12 x 12 planes).
 #include "common.h"
 
 // ---------------------------------------------------------------------------
@@ -45,13 +57,54 @@ DEV void halo_cell(int t, int &i, int &j)
     }
 }
 
-// Conserved state of the column (ci, cj) in k-plane k (possibly a ghost plane).
-template <class S>
-DEV void column_u(const KArgs &a, int slot, const Faces &nb, int ci, int cj, int k, double *u)
+// Address spaces: what no launch of this kernel writes (work list, block
+// descriptors, metric tables, dt) is read at uniform addresses through the
+// constant space, as scalar loads; addresses that came through memory or an
+// empty asm are named global, or their accesses would be flat ones.
+#define AS_CONST __attribute__((address_space(4)))
+#define AS_GLOBAL __attribute__((address_space(1)))
+template <class T> DEV const AS_CONST T *in_const(const T *p) { return (const AS_CONST T *)(uintptr_t)p; }
+
+// A k-plane of a block, or of its phi ghosts, for its columns: the value of
+// variable v of column c = ci + BI cj is c + v sv doubles behind base.  The
+// same for every lane: one address in scalar registers per plane (readfirstlane:
+// or the compiler makes a copy of every load for each of the cases).
+struct Plane {
+    unsigned long long base;
+    int sv;
+};
+
+// A value that every lane has, in scalar registers.
+DEV unsigned long long uniform64(unsigned long long x)
 {
-    const int off = ci + S::B0 * cj;
-#pragma unroll
-    for (int v = 0; v < S::NV; ++v) u[v] = cell_addr<S>(a.U, a.slabs, a.slab_stride, slot, nb, v, 0, 0, k)[off];
+    const unsigned lo = __builtin_amdgcn_readfirstlane((int)x), hi = __builtin_amdgcn_readfirstlane((int)(x >> 32));
+    return (unsigned long long)hi << 32 | lo;
+}
+
+// The double at byte offset `off` behind a uniform base plus n doubles, and
+// the other way round.
+DEV double ld_at(unsigned long long base, int n, unsigned off)
+{
+    return *(const AS_GLOBAL double *)((const AS_GLOBAL char *)(base + 8ll * n) + off);
+}
+DEV void st_at(unsigned long long base, int n, unsigned off, double x)
+{
+    *(AS_GLOBAL double *)((AS_GLOBAL char *)(base + 8ll * n) + off) = x;
+}
+
+template <class S>
+DEV Plane phi_plane(const KArgs &a, int slot, int n4, int n5, int k)
+{
+    constexpr int PL = S::B0 * S::B1;
+    const bool in = k >= 0 && k < S::B2, up = k >= S::B2;
+    const int code = in ? slot : up ? n5 : n4;
+    const int l = up ? k - S::B2 : k + 2;                 // ghost layer, 0 nearest the low side
+    const bool slab = code < 0 && code != NBR_OUTFLOW;
+    const int blk = code < 0 ? slot : code;
+    const int kk = in ? k : code < 0 ? (up ? S::B2 - 1 : 0) : (up ? l : S::B2 - 2 + l);
+    const double *const pu = a.U + (size_t)blk * S::NV * S::NC + kk * PL;
+    const double *const ps = a.slabs + (size_t)(slab ? nbr_slab(code) : 0) * a.slab_stride + l * PL;
+    return Plane{uniform64((uintptr_t)(slab ? ps : pu)), __builtin_amdgcn_readfirstlane(slab ? 2 * PL : S::NC)};
 }
 
 // Halo cells of one r- or theta-face of a block (d = 0 or 1): the cell of
@@ -90,14 +143,22 @@ DEV FaceMap face_map(const KArgs &a, int slot, const Faces &nb, int d, int side)
     return m;
 }
 
-// A radial metric record in LDS, padded from 16 to 17 doubles: the lanes of a
-// row read the records of consecutive cells, and at a 16-double stride every
-// second record falls on the same LDS banks (a 9-way conflict on each field
-// for a row of 18 lanes); at 17 the 32 lanes of a half-wave meet 32 distinct
-// bank pairs.
-struct RecRPad {
-    RecR r;
+// Metric records in LDS: the fields the kernel reads (im, ip scaled for the
+// limiter, slope_scale).  The lanes of a row read the radial records of
+// consecutive cells: 13 doubles apart the 32 lanes of a half-wave meet 32
+// distinct bank pairs (16 doubles apart every second record falls on the same
+// banks); the lanes of a column read the theta records likewise.
+struct LdsR {
+    double im, ip, ic, hm, hp, am, ap, rt, icfl, irc;
+    double om2r, gg;                             // omega^2 r, G M / r^2
     double pad;
+};
+struct LdsT {
+    double im, ip, ic, hm, hp, thm, thp, ctil, sinc, cosc, phf, icfl, isinc;
+    double s2, c2;                               // 2 omega sin, 2 omega cos
+};
+struct LdsP {
+    double im, ip, ic, hm, hp, iw;
 };
 
 // Work item of linear work index w when a.xcd_order is set: the work-groups
@@ -111,6 +172,57 @@ __device__ inline int xcd_item(int w, int n)
     return x * q + (x < rem ? x : rem) + pos;
 }
 
+// The value of the lane below (shr1) or above (shl1) in the wave.
+template <int CTRL>
+DEV double dpp64(double x)
+{
+    const long long b = __double_as_longlong(x);
+    const int lo = (int)b, hi = (int)(b >> 32);
+    const unsigned rl = __builtin_amdgcn_update_dpp(0, lo, CTRL, 0xf, 0xf, true);
+    const unsigned rh = __builtin_amdgcn_update_dpp(0, hi, CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)((unsigned long long)rh << 32 | rl));
+}
+// Adds to a double in LDS (one lane and direction at a time reaches it).
+DEV void lds_add(double *p, double x) { __hip_atomic_fetch_add(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+DEV double shr1(double x) { return dpp64<0x138>(x); }
+DEV double shl1(double x) { return dpp64<0x130>(x); }
+
+// Which wave does which face passes of a plane.  A pass is one wave's worth of
+// rows (r-faces) or columns (theta-faces); per plane a wave with columns has
+// their phi-faces and updates besides (1.54 passes' worth of instructions), one
+// without them only halo cells (about a quarter).  The passes go to the waves
+// greedily, and the odd ones to another column wave from plane to plane (phase),
+// so that the four SIMDs carry the same load: 3.5 passes' worth each on 16 x 12
+// planes (2, 2, 1 and 3 passes) instead of 4, 4, 4 and 2, and on 12 x 12 planes
+// (1, 1, 1 and 3) instead of 4, 4, 4 and 0.
+struct PassSplit {
+    unsigned begin[3];                           // first pass of wave w at bits 4 w of [phase]; wave 4: the end
+};
+constexpr PassSplit split_passes(int npass, int nwave, int ncolwave)
+{
+    PassSplit r{};
+    for (int ph = 0; ph < 3; ++ph) {
+        int load[4] = {0, 0, 0, 0}, cnt[4] = {0, 0, 0, 0};
+        for (int w = 0; w < nwave; ++w) load[w] = w < ncolwave ? 154 : 25;
+        for (int p = 0; p < npass; ++p) {
+            int best = 0;
+            for (int q = 0; q < nwave; ++q) {
+                const int w = q < ncolwave ? (q + ph) % ncolwave : q;
+                if (q == 0 || load[w] < load[best]) best = w;
+            }
+            load[best] += 100;
+            cnt[best] += 1;
+        }
+        unsigned at = 0;
+        for (int w = 0; w < nwave; ++w) {
+            r.begin[ph] |= at << (4 * w);
+            at += cnt[w];
+        }
+        r.begin[ph] |= at << (4 * nwave);
+    }
+    return r;
+}
+
 // NV: conserved variables (8, or 9 with the tracer); W: waves per SIMD the
 // register allocation targets (a tuning choice); LIM: the limiter of the
 // reconstruction (LIM_MC, the paper's, by default).
@@ -119,42 +231,36 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(W, W)))
 k_stage(KArgs a)
 {
     using S = Shape<BI, BJ, BK, NV>;
-    constexpr int PI = BI + 4, PJ = BJ + 4;
-    constexpr int NFI = (BI + 1) * BJ;
-    constexpr int NFJ = BI * (BJ + 1);
+    // LDS rows are twice an odd number of doubles apart: the lanes of a theta
+    // pass walk the rows of one column, on even bank pairs, those of the next
+    // column on the odd ones (rows of 21 and differences of 16 doubles cost 38 %
+    // of the LDS cycles in bank conflicts)
+    constexpr int PI = BI + 4 + ((BI + 4) % 4 == 2 ? 0 : 2), PJ = BJ + 4;
+    constexpr int DI = BI + (BI % 4 == 2 ? 0 : 2);
+    static_assert(PI % 4 == 2 && DI % 4 == 2, "LDS row pitch");
     constexpr int NCOL = BI * BJ;
     constexpr int NHALO = 4 * (BI + BJ);
-    static_assert(NCOL + 64 <= NT && NFI <= 2 * NT && NFJ <= 2 * NT, "plane too large for the work-group");
-    // the last wave (it owns no column) copies the next planes asynchronously into LDS
-    constexpr int CWAVE = NT / 64 - 1;
-    constexpr int NHR = 4 * BJ, NHT = 4 * BI;    // r-halo cells (first), theta-halo cells
-    constexpr int NHP = NHR * NV * 2;            // r-halo: one 4-byte piece per lane, two per double
-    constexpr int NHQ = NHR / 2 * NV;            // r-halo between same-level blocks: one 16-byte piece (two layers) per lane
-    constexpr int NTP = NHT / 2 * NV;            // theta-halo rows: one 16-byte piece (two cells) per lane
-    constexpr int NCP = NCOL / 2 * NV;           // column plane: one 16-byte piece (two cells) per lane
-    static_assert(NCOL % 2 == 0 && BI % 2 == 0 && NCOL <= CWAVE * 64, "column plane copy layout");
+    static_assert(NCOL + 64 <= NT, "plane too large for the work-group");
+    constexpr int NHR = 4 * BJ;                  // r-halo cells (first; then the theta-halo)
+    // the threads without a column take the halo cells, HIT (1 or 2) each
+    constexpr int NSP = NT - NCOL, HIT = (NHALO + NSP - 1) / NSP;
+    static_assert(HIT <= 2, "halo cells per thread without a column");
 
-    __shared__ double sW[NV][PJ][PI];
-    __shared__ __attribute__((aligned(16))) double sCol[NV][NCOL];     // conserved column plane k+2
-    __shared__ __attribute__((aligned(16))) double sHalR[NV][NHR];     // conserved r-halo of plane k+1
-    __shared__ __attribute__((aligned(16))) double sHalT[NV][NHT];     // conserved theta-halo of plane k+1
-    // per halo cell: address of variable 0 in plane 0 and the strides (doubles) per variable and plane
-    __shared__ const double *sHB[NHALO];
-    __shared__ int sHV[NHALO], sHK[NHALO];
-    __shared__ double sFi[NV][BJ][BI + 1];
-    // theta fluxes; rows padded so that the lanes of (d), which walk the rows,
-    // spread over the LDS banks (a row of 16 doubles would map every second row
-    // onto the same banks)
-    constexpr int SJ = BI % 8 == 0 ? BI + 4 : BI;
-    __shared__ double sFj[NV][BJ + 1][SJ];
-    __shared__ RecRPad sR[BI + 4];
-    __shared__ RecT sT[BJ + 4];
-    __shared__ RecP sP[BK + 4];
+    // primitives of two consecutive planes: plane k in sW[k & 1], its r/theta
+    // halos with it, and the column cells of plane k+1 in the other one (so that
+    // no thread carries them in registers through the face phases)
+    __shared__ double sW[2][NV][PJ][PI];
+    // minus the r- and theta-flux differences of a plane's cells, plane k in
+    // sD[k & 1]: zeroed, then added to by the lane of each direction (two
+    // addends on zero give the same bits in either order)
+    __shared__ double sD[2][NV][BJ][DI];
+    __shared__ LdsR sR[BI + 4];
+    __shared__ LdsT sT[BJ + 4];
+    __shared__ LdsP sP[BK + 4];
     __shared__ double sred[NT / 64];
 
     const Gas gs = a.gas;
-    const int nitems = *a.nitems;
-
+    const int nitems = *in_const(a.nitems);
     const int ks = a.ksplit;                     // parts of the march along k per block
     const int nwork = nitems * ks;
     for (int wi = blockIdx.x; wi < nwork; wi += gridDim.x) {
@@ -165,351 +271,330 @@ k_stage(KArgs a)
         asm volatile("" : "+v"(tid));
         const bool col = tid < NCOL;
         const int ci = tid % BI, cj = tid / BI;      // column owned by this thread
+        const unsigned tb = 8u * (unsigned)tid;      // its byte offset in a plane
         const int ww = a.xcd_order ? xcd_item(wi, nwork) : wi;
         const int it = ww / ks, part = ww % ks;
         const int k0 = part * BK / ks, k1 = (part + 1) * BK / ks;
-        const int slot = a.items[it];
-        // block descriptor in scalar registers (only constant indices into bd)
-        struct { int org[3]; int reflux_mask; int freg[6]; } bd;
-        const int mem = a.desc[slot].member;
-        for (int e = 0; e < 3; ++e) bd.org[e] = a.desc[slot].org[e];
-        bd.reflux_mask = a.desc[slot].reflux_mask;
-        // both r-neighbours on the same level: the two halo layers of a row are
-        // adjacent cells of the neighbour (else an outflow copy or a ghost slab)
-        const bool rpair = a.desc[slot].nbr[0] >= 0 && a.desc[slot].nbr[1] >= 0;
-        for (int e = 0; e < 6; ++e) bd.freg[e] = a.desc[slot].freg[e];
-        const Faces nb = load_faces(a.desc, slot);
-        const double dt = a.dt[mem];
+        const int slot = in_const(a.items)[it];
+        const AS_CONST BlockDesc *const bd = in_const(a.desc) + slot;
+        const int mem = bd->member, mk = bd->reflux_mask;
+        const int org0 = bd->org[0], org1 = bd->org[1], org2 = bd->org[2];
+        const int fr0 = bd->freg[0], fr1 = bd->freg[1], fr2 = bd->freg[2], fr3 = bd->freg[3], fr4 = bd->freg[4],
+                  fr5 = bd->freg[5];
+        const Faces nb{bd->nbr[0], bd->nbr[1], bd->nbr[2], bd->nbr[3], bd->nbr[4], bd->nbr[5]};
+        const double dt = in_const(a.dt)[mem];
         if (dt <= 0.0) continue;                 // member finished: state stays in place
-        const LevelGeo lg = a.geo[a.desc[slot].level];
         const double adt = a.alpha * dt;
 
-        __syncthreads();
-        for (int m = tid; m < BI + 4; m += NT) sR[m].r = lg.r[bd.org[0] + m];
-        for (int m = tid; m < BJ + 4; m += NT) sT[m] = lg.t[bd.org[1] + m];
-        for (int m = tid; m < BK + 4; m += NT) sP[m] = lg.p[bd.org[2] + m];
-        // (the metric tables are read after the barrier that ends the prologue)
-
-        // --- prologue: column primitives of planes k0 and k0+1, phi-face k0-1/2
-        // registers carried along k: Wn = W(k+1), wL = face state of cell k at
-        // k+1/2, Fm = flux at k-1/2; W(k) of the own column sits in LDS
-        double Wn[NV], wL[NV], Fm[NV];
+        // --- prologue: the loads of the first planes go out first (they need
+        // the descriptor only): column planes k0-2 .. k0+1 into P0 .. P3, or a
+        // halo cell of plane k0 into P0 (and a second one into P1).  Every
+        // thread loads all the way through (no branch: the compiler would give
+        // each side registers of its own and spill); what it has no cell for
+        // comes from its block's first column and is dropped.
+        const unsigned tbc = col ? tb : 0u;
+        const Plane q0 = phi_plane<S>(a, slot, nb.n4, nb.n5, k0 - 2), q1 = phi_plane<S>(a, slot, nb.n4, nb.n5, k0 - 1);
+        const Plane q2 = phi_plane<S>(a, slot, nb.n4, nb.n5, k0), q3 = phi_plane<S>(a, slot, nb.n4, nb.n5, k0 + 1);
+        // cell h of a thread without a column: at hp[h] + v hv[h] (bytes) in the
+        // plane, hk[h] from plane to plane; hw: its place in sW, -1: none
+        unsigned long long hp[2] = {q0.base, q1.base};
+        int hv[2] = {8 * q0.sv, 8 * q1.sv}, hk[2] = {0, 0}, hw[2] = {-1, -1};
+        {
+            const FaceMap m0 = face_map<S>(a, slot, nb, 0, 0), m1 = face_map<S>(a, slot, nb, 0, 1);
+            const FaceMap m2 = face_map<S>(a, slot, nb, 1, 0), m3 = face_map<S>(a, slot, nb, 1, 1);
+#pragma unroll
+            for (int h = 0; h < HIT; ++h) {
+                const int t = tid - NCOL + h * NSP;
+                int i, j;
+                halo_cell<BI, BJ>(t, i, j);
+                const bool rh = t < NHR;                  // r-halo, else theta-halo
+                const int idx = rh ? i : j, bd_ = rh ? BI : BJ;
+                const int side = idx >= bd_ ? 1 : 0, l = side ? idx - bd_ : idx + 2, q = rh ? j : i;
+                const int f = (rh ? 0 : 2) + side;
+                const double *fb = f == 0 ? m0.base : f == 1 ? m1.base : f == 2 ? m2.base : m3.base;
+                const int fl = f == 0 ? m0.sl : f == 1 ? m1.sl : f == 2 ? m2.sl : m3.sl;
+                const int fa = f == 0 ? m0.sa : f == 1 ? m1.sa : f == 2 ? m2.sa : m3.sa;
+                const int fk = 8 * (f == 0 ? m0.sk : f == 1 ? m1.sk : f == 2 ? m2.sk : m3.sk);
+                const int fv = 8 * (f == 0 ? m0.sv : f == 1 ? m1.sv : f == 2 ? m2.sv : m3.sv);
+                const bool have = !col && t < NHALO;
+                hw[h] = have ? (j + 2) * PI + i + 2 : -1;
+                hk[h] = have ? fk : 0;
+                hv[h] = have ? fv : hv[h];
+                hp[h] = have ? (uintptr_t)(fb + l * fl + q * fa) + (long long)k0 * fk : hp[h] + tbc;
+            }
+            if (HIT < 2) hp[1] += tbc;
+        }
+        double P0[NV], P1[NV], P2[NV], P3[NV];
+        {
+            unsigned long long x = hp[0], y = hp[1];
+#pragma unroll
+            for (int v = 0; v < NV; ++v, x += hv[0]) P0[v] = *(const AS_GLOBAL double *)x;
+#pragma unroll
+            for (int v = 0; v < NV; ++v, y += hv[1]) P1[v] = *(const AS_GLOBAL double *)y;
+        }
+#pragma unroll
+        for (int v = 0; v < NV; ++v) P2[v] = ld_at(q2.base, v * q2.sv, tbc);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) P3[v] = ld_at(q3.base, v * q3.sv, tbc);
+        const AS_CONST LevelGeo *const lg = in_const(a.geo) + bd->level;
+        const AS_CONST RecP &pm1 = in_const(lg->p)[org2 + k0 + 1], &p0 = in_const(lg->p)[org2 + k0 + 2];
+        __syncthreads();                         // the LDS of the item before is done with
+        // the metric tables (read after the barrier that ends the prologue)
+        if (tid < BI + 4) {
+            const AS_GLOBAL RecR *q = (const AS_GLOBAL RecR *)(uintptr_t)lg->r + org0 + tid;
+            sR[tid] = LdsR{slope_scale<LIM>(q->idm), slope_scale<LIM>(q->idp), q->idc, q->hm, q->hp, q->am, q->ap,
+                           q->rt, q->icfl, q->irc, a.omega * a.omega * q->rc, a.gm * IC_RCP(q->rc * q->rc), 0.0};
+        } else if (tid >= 64 && tid < 64 + BJ + 4) {
+            const AS_GLOBAL RecT *q = (const AS_GLOBAL RecT *)(uintptr_t)lg->t + org1 + tid - 64;
+            sT[tid - 64] = LdsT{slope_scale<LIM>(q->idm), slope_scale<LIM>(q->idp), q->idc, q->hm, q->hp, q->thm, q->thp,
+                                q->ctil, q->sinc, q->cosc, q->phf, q->icfl, q->isinc, 2.0 * a.omega * q->sinc,
+                                2.0 * a.omega * q->cosc};
+        } else if (tid >= 128 && tid < 128 + BK + 4) {
+            const AS_GLOBAL RecP *q = (const AS_GLOBAL RecP *)(uintptr_t)lg->p + org2 + tid - 128;
+            sP[tid - 128] = LdsP{slope_scale<LIM>(q->idm), slope_scale<LIM>(q->idp), q->idc, q->hm, q->hp, q->iw};
+        }
+        // phi-face k0-1/2; registers carried along k: wL = face state of cell k
+        // at k+1/2, Fm = flux at k-1/2; W(k) and W(k+1) of the own column sit in
+        // LDS
+        double wL[NV], Fm[NV];
         int badc = -1;                           // first non-physical input (or stage-2 output) cell of this column
         int nfr = 0, nfp = 0;                    // cells of this column the density / pressure floor acted on
-        if (col) {
-            double u[NV], w0[NV], w1[NV], lo[NV], hi[NV], R0[NV], Wc[NV];
-            column_u<S>(a, slot, nb, ci, cj, k0 - 2, u); cons_to_prim<false, NV>(u, w0, gs);
-            column_u<S>(a, slot, nb, ci, cj, k0 - 1, u); cons_to_prim<false, NV>(u, w1, gs);
-            column_u<S>(a, slot, nb, ci, cj, k0, u);     cons_to_prim<false, NV>(u, Wc, gs);
-            column_u<S>(a, slot, nb, ci, cj, k0 + 1, u); cons_to_prim<false, NV>(u, Wn, gs);
-            const RecP pm1 = lg.p[bd.org[2] + k0 + 1], p0 = lg.p[bd.org[2] + k0 + 2];
-            reconstruct<LIM, NV>(w0, w1, Wc, pm1.idm, pm1.idp, pm1.idc, pm1.hm, pm1.hp, lo, hi);
-            reconstruct<LIM, NV>(w1, Wc, Wn, p0.idm, p0.idp, p0.idc, p0.hm, p0.hp, R0, wL);
-            rusanov<2, NV>(hi, R0, Fm, gs);
-            const int r = k0 == 0 ? bd.freg[4] : -1;
-            if (r >= 0)
-                for (int v = 0; v < NV; ++v) a.freg[(size_t)r * a.reg_stride + ((size_t)v * BJ + cj) * BI + ci] = Fm[v];
-#pragma unroll
-            for (int v = 0; v < NV; ++v) sW[v][cj + 2][ci + 2] = Wc[v];
-        }
-        // halos of plane k0 and the halo address table (a halo cell's address
-        // is affine in v and in k within the block's k-range), by the threads
-        // that own no column beside the column prologue, one cell each; where
-        // the halo has more cells than they are threads, the last column
-        // threads take one cell each as well (their loads go out with the
-        // column loads; all loads first)
+        double *const W0 = &sW[0][0][0][0], *const D0 = &sD[0][0][0][0];
+        constexpr int WV = PJ * PI, WB = NV * WV, DV = BJ * DI, DB = NV * DV;     // LDS strides per variable and plane
+        int cw = (cj + 2) * PI + ci + 2, cd = cj * DI + ci;
         {
-            constexpr int NSP = NT - NCOL;
-            constexpr int NXH = NHALO > NSP ? NHALO - NSP : 0;
-            static_assert(NXH <= 64 && NHALO <= NSP + NXH, "halo cells per thread");
-            constexpr int HIT = NXH > 0 ? 1 : (NHALO + NSP - 1) / NSP;
-            const bool helper = NXH > 0 && col && tid >= NCOL - NXH;
-            const int tb = col ? (helper ? NSP + tid - (NCOL - NXH) : NHALO) : tid - NCOL;
-            if (tb < NHALO) {
-                const FaceMap fm[4] = {face_map<S>(a, slot, nb, 0, 0), face_map<S>(a, slot, nb, 0, 1),
-                                       face_map<S>(a, slot, nb, 1, 0), face_map<S>(a, slot, nb, 1, 1)};
-                double u[HIT][NV];
+            double w0[NV], w1[NV], Wc[NV], Wn[NV];
+            cons_to_prim<false, NV>(P0, w0, gs);
+            cons_to_prim<false, NV>(P1, w1, gs);
+            cons_to_prim<false, NV>(P2, Wc, gs);
+            cons_to_prim<false, NV>(P3, Wn, gs);
+            double *const Wk = W0 + (k0 & 1) * WB, *const Wk1 = W0 + (~k0 & 1) * WB;
+            const int hw0 = col ? cw : hw[0];
+            if (hw0 >= 0)
 #pragma unroll
-                for (int h = 0; h < HIT; ++h) {
-                    const int t = tb + h * NSP;
-                    if (t < NHALO) {
-                        int i, j;
-                        halo_cell<BI, BJ>(t, i, j);
-                        const bool rh = t < NHR;                  // r-halo, else theta-halo
-                        const int idx = rh ? i : j, bd_ = rh ? BI : BJ;
-                        const int side = idx >= bd_ ? 1 : 0, l = side ? idx - bd_ : idx + 2, q = rh ? j : i;
-                        const int f = (rh ? 0 : 2) + side;
-                        const FaceMap &m0 = fm[0], &m1 = fm[1], &m2 = fm[2], &m3 = fm[3];
-                        const double *fb = f == 0 ? m0.base : f == 1 ? m1.base : f == 2 ? m2.base : m3.base;
-                        const int fl = f == 0 ? m0.sl : f == 1 ? m1.sl : f == 2 ? m2.sl : m3.sl;
-                        const int fa = f == 0 ? m0.sa : f == 1 ? m1.sa : f == 2 ? m2.sa : m3.sa;
-                        const int hk = f == 0 ? m0.sk : f == 1 ? m1.sk : f == 2 ? m2.sk : m3.sk;
-                        const int hv = f == 0 ? m0.sv : f == 1 ? m1.sv : f == 2 ? m2.sv : m3.sv;
-                        const double *p0 = fb + l * fl + q * fa;
-                        sHB[t] = p0;
-                        sHV[t] = hv;
-                        sHK[t] = hk;
+                for (int v = 0; v < NV; ++v) Wk[hw0 + v * WV] = col ? Wc[v] : w0[v];
+            if (HIT > 1 && hw[1] >= 0)
 #pragma unroll
-                        for (int v = 0; v < NV; ++v) u[h][v] = p0[v * hv + k0 * hk];
-                    }
-                }
+                for (int v = 0; v < NV; ++v) Wk[hw[1] + v * WV] = w1[v];
+            if (col)
 #pragma unroll
-                for (int h = 0; h < HIT; ++h) {
-                    const int t = tb + h * NSP;
-                    if (t < NHALO) {
-                        int i, j;
-                        halo_cell<BI, BJ>(t, i, j);
-                        double w[NV];
-                        cons_to_prim<false, NV>(u[h], w, gs);
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) sW[v][j + 2][i + 2] = w[v];
-                    }
-                }
-            }
+                for (int v = 0; v < NV; ++v) Wk1[cw + v * WV] = Wn[v];
+            double lo[NV], hi[NV], R0[NV];
+            reconstruct<LIM, NV>(w0, w1, Wc, slope_scale<LIM>(pm1.idm), slope_scale<LIM>(pm1.idp), pm1.idc, pm1.hm,
+                                 pm1.hp, lo, hi);
+            reconstruct<LIM, NV>(w1, Wc, Wn, slope_scale<LIM>(p0.idm), slope_scale<LIM>(p0.idp), p0.idc, p0.hm, p0.hp,
+                                 R0, wL);
+            rusanov<2, NV>(hi, R0, Fm, gs);
+            if (k0 == 0 && fr4 >= 0 && col)
+                for (int v = 0; v < NV; ++v) st_at((uintptr_t)(a.freg + (size_t)fr4 * a.reg_stride), v * NCOL, tb, Fm[v]);
         }
-        for (int c = tid; c < NCOL; c += NT) {
-            double u[NV];
-            column_u<S>(a, slot, nb, c % BI, c / BI, k0 + 2, u);
+
+        if (col)
 #pragma unroll
-            for (int v = 0; v < NV; ++v) sCol[v][c] = u[v];
-        }
+            for (int v = 0; v < 2 * NV; ++v) D0[cd + v * DV] = 0.0;
+
+        // A lane's place in the face passes: pass t takes RPW rows, the cells
+        // rc = -1 .. BI of row t RPW + rjl on adjacent lanes, or CPW columns, the
+        // cells tc = -1 .. BJ of column t CPW + til
+        constexpr int RL = BI + 2, RPW = 64 / RL, NR = (BJ + RPW - 1) / RPW;
+        constexpr int CL = BJ + 2, CPW = 64 / CL, NTH = (BI + CPW - 1) / CPW;
+        constexpr PassSplit split = split_passes(NR + NTH, NT / 64, (NCOL + 63) / 64);
+        const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        int rc = lane % RL - 1, rjl = lane < RPW * RL ? lane / RL : BJ;
+        int tc = lane % CL - 1, til = lane < CPW * CL ? lane / CL : BI;
+        // the block's refluxed faces this column touches at r and theta
+        int crf = (ci == 0 && (mk & 1)) || (ci == BI - 1 && (mk & 2)) || (cj == 0 && (mk & 4)) || (cj == BJ - 1 && (mk & 8));
+        asm volatile("" : "+v"(rc), "+v"(tc), "+v"(rjl), "+v"(til), "+v"(cw), "+v"(cd), "+v"(crf));
+        const unsigned long long ubase = (uintptr_t)(a.Ubase + (size_t)slot * NV * S::NC);
+        const unsigned long long uout = (uintptr_t)(a.Uout + (size_t)slot * NV * S::NC);
         double rmax = 0.0;
+
+        // What a thread needs from memory in the planes ahead is asked for early,
+        // into registers.  A: the column's plane k+2 for the phi-face of plane k,
+        // asked for at the end of plane k-1; B: its U_base of plane k, asked for
+        // at the start of plane k and used after its barrier.  A thread without a
+        // column: halo cells of plane k+1.
+        double A[NV], B[NV], W2[NV], Fp[NV];
+        auto load_A = [&](int k) {
+            const Plane pl = phi_plane<S>(a, slot, nb.n4, nb.n5, k + 2);
+            hp[0] += k + 1 < k1 ? hk[0] : 0;
+            unsigned long long x = col ? pl.base + tb : hp[0];
+            const int xs = col ? 8 * pl.sv : hv[0];
+#pragma unroll
+            for (int v = 0; v < NV; ++v, x += xs) A[v] = *(const AS_GLOBAL double *)x;
+        };
+        auto load_B = [&](int k) {
+            hp[1] += k + 1 < k1 ? hk[1] : 0;
+            unsigned long long y = col ? ubase + 8ll * k * NCOL + tb : hp[1];
+            const int ys = col ? 8 * S::NC : hv[1];
+#pragma unroll
+            for (int v = 0; v < NV; ++v, y += ys) B[v] = *(const AS_GLOBAL double *)y;
+        };
+        load_A(k0);
         __syncthreads();
 
-        for (int k = k0; k < k1; ++k) {
-            // plane k with its i/j halos is in LDS
-            // (c) r-faces of the plane.  A row of lanes takes the cells c = -1 .. BI
-            // of one j: each lane reconstructs its cell's two face states once,
-            // passes the upper one to the next lane through LDS (a row lies within
-            // one wave, whose LDS accesses stay in order) and computes the flux at
-            // its lower face f = c, between cells c-1 and c.
-            {
-                constexpr int RL = BI + 2, RPW = 64 / RL;
-                static_assert((BJ + RPW - 1) / RPW <= NT / 64, "r-face rows per wave");
-                const int lane = tid & 63, c = lane % RL - 1;
-                const int j = (tid >> 6) * RPW + lane / RL;
-                const bool act = lane < RPW * RL && j < BJ;
-                double lo[NV], hi[NV];
-                if (act) {
-                    double wm[NV], w0[NV], wp[NV];
+        // One barrier per plane: behind it a column thread updates its cell of
+        // the plane whose faces are done, then the waves go on to the faces of
+        // the next one, whose primitives were complete at the same barrier.
+#pragma unroll 1
+        for (int k = k0;; ++k) {
+            if (k > k0 && col) {
+                // update of cell (ci, cj, kc)
+                const int kc = k - 1;
+                double *const Wc = W0 + (kc & 1) * WB, *const Dc = D0 + (kc & 1) * DB;
+                const LdsR &rr = sR[ci + 2];
+                const LdsT &tt = sT[cj + 2];
+                double w[NV], acc[NV];
 #pragma unroll
-                    for (int v = 0; v < NV; ++v) {
-                        wm[v] = sW[v][j + 2][c + 1];
-                        w0[v] = sW[v][j + 2][c + 2];
-                        wp[v] = sW[v][j + 2][c + 3];
-                    }
-                    const RecR rc = sR[c + 2].r;
-                    reconstruct<LIM, NV>(wm, w0, wp, rc.idm, rc.idp, rc.idc, rc.hm, rc.hp, lo, hi);
-                    if (c < BI)
+                for (int v = 0; v < NV; ++v) w[v] = Wc[cw + v * WV];
 #pragma unroll
-                        for (int v = 0; v < NV; ++v) sFi[v][j][c + 1] = hi[v];
-                }
-                __builtin_amdgcn_wave_barrier();
-                if (act && c >= 0) {
-                    double L[NV], fx[NV];
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) L[v] = sFi[v][j][c];
-                    rusanov<0, NV>(L, lo, fx, gs);
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) sFi[v][j][c] = fx[v];
-                    if (c == 0 || c == BI) {      // raw flux at a coarse-fine face, for the reflux
-                        const int r = c == 0 ? bd.freg[0] : bd.freg[1];
-                        if (r >= 0)
-                            for (int v = 0; v < NV; ++v)
-                                a.freg[(size_t)r * a.reg_stride + ((size_t)v * BK + k) * BJ + j] = fx[v];
-                    }
-                }
-            }
-            // (d) theta-faces of the plane, the same way along j: a column of lanes
-            // takes the cells c = -1 .. BJ of one i (the columns of a wave interleaved)
-            {
-                constexpr int CL = BJ + 2, CPW = 64 / CL;
-                static_assert((BI + CPW - 1) / CPW <= NT / 64, "theta-face columns per wave");
-                const int lane = tid & 63, c = lane / CPW - 1;
-                const int i = (tid >> 6) * CPW + lane % CPW;
-                const bool act = lane < CPW * CL && i < BI;
-                double lo[NV], hi[NV];
-                if (act) {
-                    double wm[NV], w0[NV], wp[NV];
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) {
-                        wm[v] = sW[v][c + 1][i + 2];
-                        w0[v] = sW[v][c + 2][i + 2];
-                        wp[v] = sW[v][c + 3][i + 2];
-                    }
-                    const RecT rc = sT[c + 2];
-                    reconstruct<LIM, NV>(wm, w0, wp, rc.idm, rc.idp, rc.idc, rc.hm, rc.hp, lo, hi);
-                    if (c < BJ)
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) sFj[v][c + 1][i] = hi[v];
-                }
-                __builtin_amdgcn_wave_barrier();
-                if (act && c >= 0) {
-                    double L[NV], fx[NV];
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) L[v] = sFj[v][c][i];
-                    rusanov<1, NV>(L, lo, fx, gs);
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) sFj[v][c][i] = fx[v];
-                    if (c == 0 || c == BJ) {
-                        const int r = c == 0 ? bd.freg[2] : bd.freg[3];
-                        if (r >= 0)
-                            for (int v = 0; v < NV; ++v)
-                                a.freg[(size_t)r * a.reg_stride + ((size_t)v * BK + k) * BI + i] = fx[v];
-                    }
-                }
-            }
-            if (k + 1 < k1 && (tid >> 6) == CWAVE) {
-                // the last wave, done with its LDS work of this phase, starts the
-                // copies of the conserved r/theta halo of plane k+1 into LDS (read
-                // before the last barrier); they land while the other waves finish
-                // the plane's fluxes (a wave's LDS accesses wait for its own copies
-                // into LDS, so it issues them after its own reads)
-                const int lane = tid & 63;
-                typedef __attribute__((address_space(3))) char lds_t;
-                if (rpair) {
-#pragma unroll 2
-                    for (int q = 0; q * 64 < NHQ; ++q) {
-                        const int g = q * 64 + lane;
-                        if (g < NHQ) {
-                            const int v = g / (NHR / 2), cell = 2 * (g % (NHR / 2));
-                            const double *src = sHB[cell] + v * sHV[cell] + (k + 1) * sHK[cell];
-                            __builtin_amdgcn_global_load_lds((const void *)src,
-                                                             (lds_t *)((lds_t *)&sHalR[0][0] + q * 1024), 16, 0, 0);
-                        }
-                    }
-                } else {
-#pragma unroll 2
-                    for (int q = 0; q * 64 < NHP; ++q) {
-                        const int g = q * 64 + lane;
-                        if (g < NHP) {
-                            const int v = g / (2 * NHR), cell = (g >> 1) % NHR, half = g & 1;
-                            const char *src = (const char *)(sHB[cell] + v * sHV[cell] + (k + 1) * sHK[cell]) + 4 * half;
-                            __builtin_amdgcn_global_load_lds((const void *)src,
-                                                             (lds_t *)((lds_t *)&sHalR[0][0] + q * 256), 4, 0, 0);
-                        }
-                    }
-                }
-#pragma unroll 2
-                for (int q = 0; q * 64 < NTP; ++q) {
-                    // theta-halo rows are contiguous in i in a block, a slab or an outflow copy
-                    const int g = q * 64 + lane;
-                    if (g < NTP) {
-                        const int v = g / (NHT / 2), cell = NHR + 2 * (g % (NHT / 2));
-                        const double *src = sHB[cell] + v * sHV[cell] + (k + 1) * sHK[cell];
-                        __builtin_amdgcn_global_load_lds((const void *)src,
-                                                         (lds_t *)((lds_t *)&sHalT[0][0] + q * 1024), 16, 0, 0);
-                    }
-                }
-            }
-
-            // (e) phi-face k+1/2 of the column: cells k (from LDS), k+1 and k+2
-            double Fp[NV], Wnext[NV];
-            if (col) {
-                double u[NV], W2[NV], lo1[NV], w0[NV];
-#pragma unroll
-                for (int v = 0; v < NV; ++v) u[v] = sCol[v][tid];
-                cons_to_prim<false, NV>(u, W2, gs);
-#pragma unroll
-                for (int v = 0; v < NV; ++v) w0[v] = sW[v][cj + 2][ci + 2];
-                const RecP pk1 = sP[k + 3];
-                double hi1[NV];
-                reconstruct<LIM, NV>(w0, Wn, W2, pk1.idm, pk1.idp, pk1.idc, pk1.hm, pk1.hp, lo1, hi1);
-                rusanov<2, NV>(wL, lo1, Fp, gs);
-                if (k == BK - 1) {
-                    const int r = bd.freg[5];
-                    if (r >= 0)
-                        for (int v = 0; v < NV; ++v) a.freg[(size_t)r * a.reg_stride + ((size_t)v * BJ + cj) * BI + ci] = Fp[v];
-                }
+                for (int v = 0; v < NV; ++v) acc[v] = Dc[cd + v * DV];
+                const double rt = rr.rt, iw = sP[kc + 2].iw, kf = rt * tt.phf * iw;
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
-                    wL[v] = hi1[v];
-                    Wnext[v] = Wn[v];
-                    Wn[v] = W2[v];
+                    Wc[cw + v * WV] = W2[v];         // own cell of plane kc+2, where plane kc's was
+                    Dc[cd + v * DV] = 0.0;
                 }
-            }
-            __syncthreads();
-
-            // (g) update of cell (ci, cj, k)
-            if (col) {
-                const RecP pk = sP[k + 2];
-                const RecR rr = sR[ci + 2].r;
-                const RecT tt = sT[cj + 2];
-                double w[NV];
-#pragma unroll
-                for (int v = 0; v < NV; ++v) w[v] = sW[v][cj + 2][ci + 2];
-                if (badc < 0 && unphysical<NV>(w)) badc = ci + BI * (cj + BJ * k);
-                double acc[NV];
-                const double thm = rr.rt * tt.thm, thp = rr.rt * tt.thp;
-                const double kf = rr.rt * tt.phf * pk.iw;
+                if (badc < 0 && unphysical<NV>(w)) badc = tid + NCOL * kc;
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
-                    acc[v] = -(rr.ap * sFi[v][cj][ci + 1] - rr.am * sFi[v][cj][ci])
-                             - (thp * sFj[v][cj + 1][ci] - thm * sFj[v][cj][ci])
-                             - kf * (Fp[v] - Fm[v]);
+                    acc[v] = acc[v] - kf * (Fp[v] - Fm[v]);
+                    Fm[v] = Fp[v];
                 }
-                if (!a.cart) add_sources(w, rr.rt, tt.ctil, rr.rc, tt.sinc, tt.cosc, a.omega, a.gm, acc);
-                const size_t base = cidx<S>(slot, 0, ci, cj, k);
+                if (!a.cart) {
+                    const double c = rr.om2r * tt.sinc;
+                    add_sources(w, rt, tt.ctil, tt.s2, tt.c2, fma(c, tt.sinc, -rr.gg), c * tt.cosc, acc);
+                }
+                const unsigned long long uo = uout + 8ll * kc * NCOL;
                 double unew[NV];
 #pragma unroll
-                for (int v = 0; v < NV; ++v) unew[v] = a.Ubase[base + (size_t)v * S::NC] + adt * acc[v];
+                for (int v = 0; v < NV; ++v) unew[v] = B[v] + adt * acc[v];
                 // floors now, or after the reflux for cells on a coarse-fine face
-                const int mk = bd.reflux_mask;
-                const bool rf = (ci == 0 && (mk & 1)) || (ci == BI - 1 && (mk & 2)) || (cj == 0 && (mk & 4))
-                             || (cj == BJ - 1 && (mk & 8)) || (k == 0 && (mk & 16)) || (k == BK - 1 && (mk & 32));
-                if (!rf) {
-                    const int f = apply_floors(unew, gs, a.rho_floor, a.p_floor);
-                    nfr += f & 1;
-                    nfp += f >> 1;
-                }
-#pragma unroll
-                for (int v = 0; v < NV; ++v) a.Uout[base + (size_t)v * S::NC] = unew[v];
-                if (a.want_rate && !rf) {            // refluxed cells: after the reflux
+                const bool rf_cell = crf || (kc == 0 && (mk & 16)) || (kc == BK - 1 && (mk & 32));
+                if (!rf_cell) {
                     cons_to_prim<false, NV>(unew, w, gs);
-                    // the step's result: a non-finite value created in this stage
-                    // would otherwise drop out of the CFL maximum unnoticed
-                    if (badc < 0 && unphysical<NV>(w)) badc = ci + BI * (cj + BJ * k);
-                    const double rate = (fabs(w[1]) + fast_speed<0>(w, gs)) * rr.icfl
-                                      + (fabs(w[2]) + fast_speed<1>(w, gs)) * rr.irc * tt.icfl
-                                      + (fabs(w[3]) + fast_speed<2>(w, gs)) * rr.irc * tt.isinc * pk.iw;
-                    rmax = rate > rmax ? rate : rmax;
-                }
-#pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    Fm[v] = Fp[v];
-                    sW[v][cj + 2][ci + 2] = Wnext[v];   // own cell of plane k+1; read back in (e) and (g)
-                }
-            } else if (k + 1 < k1 && (tid >> 6) == CWAVE) {
-                // (p) meanwhile the last wave (no column) starts the copy of the
-                // column plane k+3 from HBM into LDS (read in (e) of the next plane;
-                // this plane's copy was read before the last barrier), waits for it
-                // and for the halo copies of plane k+1, and converts that halo to
-                // primitives
-                const int lane = tid & 63;
-                typedef __attribute__((address_space(3))) char lds_t;
-#pragma unroll 2
-                for (int q = 0; q * 64 < NCP; ++q) {
-                    const int g = q * 64 + lane;
-                    if (g < NCP) {
-                        const int v = g / (NCOL / 2), pr = g % (NCOL / 2);
-                        const double *base = cell_addr<S>(a.U, a.slabs, a.slab_stride, slot, nb, v, 0, 0, k + 3);
-                        __builtin_amdgcn_global_load_lds((const void *)(base + 2 * pr),
-                                                         (lds_t *)((lds_t *)&sCol[0][0] + q * 1024), 16, 0, 0);
+                    if (unew[0] < a.rho_floor || w[4] < a.p_floor) {         // rare
+                        const int f = apply_floors(unew, gs, a.rho_floor, a.p_floor);
+                        nfr += f & 1;
+                        nfp += f >> 1;
+                        cons_to_prim<false, NV>(unew, w, gs);
                     }
                 }
-                __builtin_amdgcn_s_waitcnt(0);           // column plane k+3 and the halo have landed
-#pragma unroll 1
-                for (int t = lane; t < NHALO; t += 64) {
-                    int i, j;
-                    halo_cell<BI, BJ>(t, i, j);
-                    double u[NV], w8[NV];
 #pragma unroll
-                    for (int v = 0; v < NV; ++v) u[v] = t < NHR ? sHalR[v][t] : sHalT[v][t - NHR];
-                    cons_to_prim<false, NV>(u, w8, gs);
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) sW[v][j + 2][i + 2] = w8[v];
+                for (int v = 0; v < NV; ++v) st_at(uo, v * S::NC, tb, unew[v]);
+                if (a.want_rate && !rf_cell) {       // refluxed cells: after the reflux
+                    // the step's result: a non-finite value created in this stage
+                    // would otherwise drop out of the CFL maximum unnoticed
+                    if (badc < 0 && unphysical<NV>(w)) badc = tid + NCOL * kc;
+                    const double rate = cell_rate_of(w, rr.icfl, rr.irc * tt.icfl, rr.irc * tt.isinc * iw, gs);
+                    rmax = rate > rmax ? rate : rmax;
                 }
             }
+            if (k == k1) break;
+            double *const Wk = W0 + (k & 1) * WB, *const Wk1 = W0 + (~k & 1) * WB, *const Dk = D0 + (k & 1) * DB;
+            load_B(k);
+
+            // this wave's face passes.  Every lane goes through (those without a
+            // cell, or whose face or difference is no use, on any values): each
+            // reconstructs its cell's two face states, takes the upper one of the
+            // cell below from its lane, and computes the flux at its lower face;
+            // the flux at its upper face comes back from the lane above, and the
+            // cell's difference goes to sD.
+            const int ph = k % 3;
+            const unsigned bs = (ph == 0 ? split.begin[0] : ph == 1 ? split.begin[1] : split.begin[2]) >> (4 * wave);
+            const int t0 = bs & 15, t1 = (bs >> 4) & 15;
+#pragma unroll 1
+            for (int t = t0; t < t1 && t < NR; ++t) {            // r
+                const int j = t * RPW + rjl;
+                const bool act = j < BJ;
+                const int at = act ? (j + 2) * PI + rc + 1 : 0;
+                double wm[NV], w0[NV], wp[NV], lo[NV], hi[NV], L[NV], fx[NV];
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    wm[v] = Wk[at + v * WV];
+                    w0[v] = Wk[at + v * WV + 1];
+                    wp[v] = Wk[at + v * WV + 2];
+                }
+                const LdsR &m = sR[rc + 2];
+                reconstruct<LIM, NV>(wm, w0, wp, m.im, m.ip, m.ic, m.hm, m.hp, lo, hi);
+#pragma unroll
+                for (int v = 0; v < NV; ++v) L[v] = shr1(hi[v]);
+                rusanov<0, NV>(L, lo, fx, gs);
+                const double ap = m.ap, am = m.am;
+#pragma unroll
+                for (int v = 0; v < NV; ++v) L[v] = fma(-ap, shl1(fx[v]), am * fx[v]);
+                if (act && rc >= 0 && rc < BI)
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) lds_add(Dk + j * DI + rc + v * DV, L[v]);
+                if (act && (rc == 0 || rc == BI)) {      // raw flux at a coarse-fine face, for the reflux
+                    const int r = rc == 0 ? fr0 : fr1;
+                    if (r >= 0)
+                        for (int v = 0; v < NV; ++v)
+                            a.freg[(size_t)r * a.reg_stride + ((size_t)v * BK + k) * BJ + j] = fx[v];
+                }
+            }
+#pragma unroll 1
+            for (int t = t0 > NR ? t0 - NR : 0; t < t1 - NR; ++t) {    // theta
+                const int i = t * CPW + til;
+                const bool act = i < BI;
+                const int at = act ? (tc + 1) * PI + i + 2 : 0;
+                double wm[NV], w0[NV], wp[NV], lo[NV], hi[NV], L[NV], fx[NV];
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    wm[v] = Wk[at + v * WV];
+                    w0[v] = Wk[at + v * WV + PI];
+                    wp[v] = Wk[at + v * WV + 2 * PI];
+                }
+                const LdsT &m = sT[tc + 2];
+                reconstruct<LIM, NV>(wm, w0, wp, m.im, m.ip, m.ic, m.hm, m.hp, lo, hi);
+#pragma unroll
+                for (int v = 0; v < NV; ++v) L[v] = shr1(hi[v]);
+                rusanov<1, NV>(L, lo, fx, gs);
+                const double rt = sR[act ? i + 2 : 0].rt, thp = rt * m.thp, thm = rt * m.thm;
+#pragma unroll
+                for (int v = 0; v < NV; ++v) L[v] = fma(-thp, shl1(fx[v]), thm * fx[v]);
+                if (act && tc >= 0 && tc < BJ)
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) lds_add(Dk + tc * DI + i + v * DV, L[v]);
+                if (act && (tc == 0 || tc == BJ)) {
+                    const int r = tc == 0 ? fr2 : fr3;
+                    if (r >= 0)
+                        for (int v = 0; v < NV; ++v)
+                            a.freg[(size_t)r * a.reg_stride + ((size_t)v * BK + k) * BI + i] = fx[v];
+                }
+            }
+
+            // phi-face k+1/2 of the column: cells k, k+1 (LDS) and k+2 (memory)
+            if (col) {
+                double lo1[NV], hi1[NV], w0[NV], w1[NV];
+                cons_to_prim<false, NV>(A, W2, gs);
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    w0[v] = Wk[cw + v * WV];
+                    w1[v] = Wk1[cw + v * WV];
+                }
+                const LdsP &m = sP[k + 3];
+                reconstruct<LIM, NV>(w0, w1, W2, m.im, m.ip, m.ic, m.hm, m.hp, lo1, hi1);
+                rusanov<2, NV>(wL, lo1, Fp, gs);
+                if (k == BK - 1 && fr5 >= 0) {
+                    int r = fr5;
+                    asm volatile("" : "+s"(r));     // its addresses are formed here, not kept through the loop
+                    for (int v = 0; v < NV; ++v) st_at((uintptr_t)(a.freg + (size_t)r * a.reg_stride), v * NCOL, tb, Fp[v]);
+                }
+#pragma unroll
+                for (int v = 0; v < NV; ++v) wL[v] = hi1[v];
+            } else if (k + 1 < k1) {
+                // the other threads turn the halo of plane k+1 into primitives
+#pragma unroll
+                for (int h = 0; h < HIT; ++h)
+                    if (hw[h] >= 0) {
+                        double w[NV];
+                        cons_to_prim<false, NV>(h == 0 ? A : B, w, gs);
+#pragma unroll
+                        for (int v = 0; v < NV; ++v) Wk1[hw[h] + v * WV] = w[v];
+                    }
+            }
+            if (k + 1 < k1) load_A(k + 1);
             __syncthreads();
         }
         if (col && badc >= 0 && atomicCAS(&a.bad[2 * mem], 0, slot + 1) == 0) a.bad[2 * mem + 1] = badc;
