@@ -441,7 +441,10 @@ typedef struct {
  * size (and reads the cache's results for other sizes): after each regrid the
  * schedule of the new size is used, or, for a size without one, two waves per
  * SIMD, one work-group per work item and the smallest k-split giving at least
- * 512 work-groups.  Without any tuning call that rule applies from the start. */
+ * 512 work-groups.  Without any tuning call that rule applies from the start.
+ * Work lists too short to fill the device (12^3 blocks: up to about 340 of
+ * them) run on a second stage kernel without such a schedule, with the same
+ * bits, unless ic_set_tuning has set a schedule. */
 ic_status ic_autotune(ic_sim *sim, const char *cache_path, int reps, ic_tune_info *out);
 
 /* Force a schedule (waves_per_simd, grid, xcd_order, ksplit of *tune); it is

@@ -171,6 +171,7 @@ struct IndicatorParams {
 // Launch wrappers per block shape (kernels.hip, stage.hip); the runtime calls these.
 struct Launchers {
     void (*stage)(dim3, hipStream_t, const KArgs &, int waves, int limiter);
+    void (*tile)(dim3, hipStream_t, const KArgs &, int kz, int limiter);
     void (*hancock)(dim3, hipStream_t, const KArgs &, int limiter);
     void (*divb)(dim3, hipStream_t, const KArgs &);
     void (*clean)(dim3, hipStream_t, const KArgs &);
@@ -190,6 +191,7 @@ void launch_time(hipStream_t s, double *t, const double *dt, long *nsteps, int n
 // kernel entry points (stage.hip: k_stage and its launcher; kernels.hip: the rest)
 template <int BI, int BJ, int BK, int NV, int W, int LIM> __global__ void k_stage(KArgs a);
 template <int BI, int BJ, int BK, int NV> void launch_stage(dim3 g, hipStream_t s, const KArgs &a, int waves, int limiter);
+template <int BI, int BJ, int BK, int NV> void launch_tile(dim3 g, hipStream_t s, const KArgs &a, int kz, int limiter);
 template <int BI, int BJ, int BK, int NV, int LIM> __global__ void k_hancock(KArgs a);
 template <int BI, int BJ, int BK, int NV> __global__ void k_divb(KArgs a);
 template <int BI, int BJ, int BK, int NV> __global__ void k_clean(KArgs a);

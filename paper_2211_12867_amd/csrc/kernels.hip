@@ -1115,7 +1115,7 @@ struct L {
     }
     static Launchers get()
     {
-        return Launchers{&launch_stage<BI, BJ, BK, NV>, &launch_hancock<BI, BJ, BK, NV>, &divb, &clean, &slabs,
+        return Launchers{&launch_stage<BI, BJ, BK, NV>, &launch_tile<BI, BJ, BK, NV>, &launch_hancock<BI, BJ, BK, NV>, &divb, &clean, &slabs,
                          &reflux, &rate, &indicator, &move, &sample};
     }
 };

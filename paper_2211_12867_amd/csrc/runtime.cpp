@@ -345,6 +345,7 @@ struct ic_sim {
     double omega_code = 0.0, gm_code = 0.0;
     hipStream_t stream = nullptr;
     bool own_stream = false;
+    int n_cu = 256;                 // compute units of the device
     Launchers L{};
     bool poisoned = false;
 
@@ -1127,6 +1128,29 @@ int stage_grid(const ic_sim *s)
     return s->tune_grid > 0 ? std::min(n, s->tune_grid) : n;
 }
 
+// Planes per work-group of the stage kernel for short work lists (launch_tile),
+// 0: the marching kernel.  One or two planes while every work-group has a CU of
+// its own (the fewer planes, the shorter each work-group's chain: 8 blocks of
+// 12^3 14.8, 17 and 22 us with 1, 2 and 4 planes, 40 blocks 20.7, 20 and 26 us,
+// the marching kernel 21.5 and 25 us); four planes up to four work-groups per CU
+// (160 blocks 40 us against 45, 320 blocks 69 against 71; 512 blocks 97 against
+// 84), but not on planes of more than 160 cells, which fill the marching
+// kernel's waves (48 blocks of 16 x 12 x 12: 29 us against 27).  Blocks of 4^3
+// cells leave most lanes of the marching kernel without a column: always here
+// (1,024 blocks: 24 us against 42).  A schedule set by ic_set_tuning is one of
+// the marching kernel.
+int tile_planes(const ic_sim *s)
+{
+    if (s->tune_pinned) return 0;
+    const long plane = (long)s->B[0] * s->B[1], n = s->n_items;
+    for (int kz : {1, 2})
+        if (n * (s->B[2] / kz) <= s->n_cu) return kz;
+    if (plane < 64 || (plane <= 160 && n * (s->B[2] / 4) <= 4L * s->n_cu)) return 4;
+    return 0;
+}
+
+int tile_grid(const ic_sim *s, int kz) { return quant_grid(s->n_items * (s->B[2] / kz), 1 << 30); }
+
 // ghost-slab launches: one work-group per task of the pass (the kernels
 // stride over the device-side task ranges, so any size is correct)
 int slab_grid(const ic_sim *s, int pass)
@@ -1141,7 +1165,8 @@ int reflux_grid(const ic_sim *s) { return s->any_reflux ? quant_grid(s->n_rf_tas
 // launch sizes of a step; a captured step graph is re-made when they change
 std::vector<int> launch_sig(const ic_sim *s)
 {
-    return {stage_grid(s), slab_grid(s, 0), slab_grid(s, 1), reflux_grid(s)};
+    const int kz = tile_planes(s);
+    return {kz, kz ? tile_grid(s, kz) : stage_grid(s), slab_grid(s, 0), slab_grid(s, 1), reflux_grid(s)};
 }
 
 void fill_ghosts(ic_sim *s, double *Uin, double tfrac)
@@ -1163,18 +1188,21 @@ void stage(ic_sim *s, double *Uin, double *Ubase, double *Uout, double alpha, in
     a.Uout = Uout;
     a.alpha = alpha;
     a.want_rate = want_rate;
-    const int g = stage_grid(s);
+    auto launch = [&] {
+        if (const int kz = tile_planes(s)) s->L.tile(dim3(tile_grid(s, kz)), s->stream, a, kz, s->phys.limiter);
+        else s->L.stage(dim3(stage_grid(s)), s->stream, a, s->tune_waves, s->phys.limiter);
+    };
     if (s->timing) {
         hipEvent_t e0, e1;
         HIPCHECK(hipEventCreate(&e0));
         HIPCHECK(hipEventCreate(&e1));
         HIPCHECK(hipEventRecord(e0, s->stream));
-        s->L.stage(dim3(g), s->stream, a, s->tune_waves, s->phys.limiter);
+        launch();
         HIPCHECK(hipEventRecord(e1, s->stream));
         s->ev.push_back(e0);
         s->ev.push_back(e1);
     } else {
-        s->L.stage(dim3(g), s->stream, a, s->tune_waves, s->phys.limiter);
+        launch();
     }
     if (s->any_reflux) s->L.reflux(dim3(reflux_grid(s)), s->stream, a, s->rf_tasks.p, s->rf_ranges.p, s->rf_ntasks.p);
 }
@@ -2132,6 +2160,7 @@ ic_status ic_create(const ic_grid_cfg *grid, const ic_phys_cfg *phys, const ic_w
         }
         int dev = 0;
         HIPCHECK(hipGetDevice(&dev));
+        HIPCHECK(hipDeviceGetAttribute(&s->n_cu, hipDeviceAttributeMultiprocessorCount, dev));
         // levels
         s->lv.resize(s->max_level + 2);
         for (int l = 1; l <= s->max_level; ++l) build_level(s, l);

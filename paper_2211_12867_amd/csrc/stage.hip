@@ -107,33 +107,33 @@ DEV Plane phi_plane(const KArgs &a, int slot, int n4, int n5, int k)
     return Plane{uniform64((uintptr_t)(slab ? ps : pu)), __builtin_amdgcn_readfirstlane(slab ? 2 * PL : S::NC)};
 }
 
-// Halo cells of one r- or theta-face of a block (d = 0 or 1): the cell of
-// layer l (0 nearest the low side), in-face index a (j on an r-face, i on a
-// theta-face), plane k and variable v is at base + l sl + a sa + k sk + v sv
-// in the same-level neighbour, the block's own edge (outflow) or the ghost
-// slab -- the cases of cell_addr, resolved once per face.
+// Halo cells behind one face of a block (direction d, face code as in
+// BlockDesc::nbr): the cell of layer l (0 nearest the low side), in-face index
+// a (j on an r-face, i on a theta-face, the column on a phi-face), plane k (not
+// on a phi-face) and variable v is at base + l sl + a sa + k sk + v sv in the
+// same-level neighbour, the block's own edge (outflow) or the ghost slab -- the
+// cases of cell_addr, resolved once per face.
 struct FaceMap {
     const double *base;
     int sl, sa, sk, sv;
 };
 
 template <class S>
-DEV FaceMap face_map(const KArgs &a, int slot, const Faces &nb, int d, int side)
+DEV FaceMap face_map(const KArgs &a, int slot, int code, int d, int side)
 {
-    const int Bd = S::dim(d);
-    const int code = face_code(nb, 2 * d + side);
+    constexpr int PL = S::B0 * S::B1;
+    const int Bd = S::dim(d), st = d == 0 ? 1 : d == 1 ? S::B0 : PL;        // cells and stride along d in a block
     FaceMap m;
     if (code >= 0 || code == NBR_OUTFLOW) {
         const int blk = code >= 0 ? code : slot;
         const int i0 = code >= 0 ? (side ? 0 : Bd - 2) : (side ? Bd - 1 : 0);   // layer 0 along d
-        const int sl = code >= 0 ? 1 : 0;
-        m.base = a.U + (size_t)blk * S::NV * S::NC + (d == 0 ? i0 : S::B0 * i0);
-        m.sl = d == 0 ? sl : S::B0 * sl;
+        m.base = a.U + (size_t)blk * S::NV * S::NC + st * i0;
+        m.sl = code >= 0 ? st : 0;
         m.sa = d == 0 ? S::B0 : 1;
-        m.sk = S::B0 * S::B1;
+        m.sk = PL;
         m.sv = S::NC;
     } else {
-        const int FA = d == 0 ? S::B1 : S::B0, FB = S::B2;    // slab layout of cell_addr
+        const int FA = d == 0 ? S::B1 : S::B0, FB = d == 2 ? S::B1 : S::B2;     // slab layout of cell_addr
         m.base = a.slabs + (size_t)nbr_slab(code) * a.slab_stride;
         m.sl = FB * FA;
         m.sa = 1;
@@ -182,10 +182,98 @@ DEV double dpp64(double x)
     const unsigned rh = __builtin_amdgcn_update_dpp(0, hi, CTRL, 0xf, 0xf, true);
     return __longlong_as_double((long long)((unsigned long long)rh << 32 | rl));
 }
+// Pitch of rows of n doubles in LDS: the next number that is 2 modulo 4.
+constexpr int tile_pitch(int n) { return n + (6 - n % 4) % 4; }
+
 // Adds to a double in LDS (one lane and direction at a time reaches it).
 DEV void lds_add(double *p, double x) { __hip_atomic_fetch_add(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
 DEV double shr1(double x) { return dpp64<0x138>(x); }
 DEV double shl1(double x) { return dpp64<0x130>(x); }
+
+// One cell's bookkeeping over a work item.
+struct CellLog {
+    int bad = -1;            // first non-physical stage input or second-stage result: its cell
+    int nfr = 0, nfp = 0;    // cell updates the density / pressure floor acted on
+    double rmax = 0.0;       // largest CFL rate
+};
+
+// Update of one cell: u (U_base in, U_out out) += adt (acc + sources), acc minus
+// the flux differences and w the stage input's primitives (overwritten); then
+// the floors and, in the second stage, the output check and the CFL rate,
+// unless the cell lies on a refluxed face (they follow the reflux).
+template <int NV>
+DEV void update_cell(const KArgs &a, const Gas &gs, const LdsR &rr, const LdsT &tt, double iw, double adt, bool refluxed,
+                     int cell, double *w, double *acc, double *u, CellLog &log)
+{
+    if (log.bad < 0 && unphysical<NV>(w)) log.bad = cell;
+    if (!a.cart) {
+        const double c = rr.om2r * tt.sinc;
+        add_sources(w, rr.rt, tt.ctil, tt.s2, tt.c2, fma(c, tt.sinc, -rr.gg), c * tt.cosc, acc);
+    }
+#pragma unroll
+    for (int v = 0; v < NV; ++v) u[v] = u[v] + adt * acc[v];
+    if (refluxed) return;
+    cons_to_prim<false, NV>(u, w, gs);
+    if (u[0] < a.rho_floor || w[4] < a.p_floor) {                // rare
+        const int f = apply_floors(u, gs, a.rho_floor, a.p_floor);
+        log.nfr += f & 1;
+        log.nfp += f >> 1;
+        cons_to_prim<false, NV>(u, w, gs);
+    }
+    if (a.want_rate) {
+        // the step's result: a non-finite value created in this stage would
+        // otherwise drop out of the CFL maximum unnoticed
+        if (log.bad < 0 && unphysical<NV>(w)) log.bad = cell;
+        const double rate = cell_rate_of(w, rr.icfl, rr.irc * tt.icfl, rr.irc * tt.isinc * iw, gs);
+        log.rmax = rate > log.rmax ? rate : log.rmax;
+    }
+}
+
+// The end of a work item: a member's first bad cell, its floor counts, and the
+// item's CFL maximum as part `part` of `parts` of the block (the last part
+// clears the entries beyond).
+template <int THREADS>
+DEV void end_item(const KArgs &a, int slot, int mem, int part, int parts, const CellLog &log, double *sred)
+{
+    if (log.bad >= 0 && atomicCAS(&a.bad[2 * mem], 0, slot + 1) == 0) a.bad[2 * mem + 1] = log.bad;
+    if (log.nfr | log.nfp) {
+        atomicAdd(&a.floors[2 * mem], (unsigned long long)log.nfr);
+        atomicAdd(&a.floors[2 * mem + 1], (unsigned long long)log.nfp);
+    }
+    if (a.want_rate) {
+        const int tid = threadIdx.x;
+        double m = wave_max(log.rmax);
+        if ((tid & 63) == 0) sred[tid >> 6] = m;
+        __syncthreads();
+        if (tid < 64) {
+            m = wave_max(tid < THREADS / 64 ? sred[tid] : 0.0);
+            double *const r = a.rate + (size_t)slot * KSPLIT_MAX;
+            if (tid == part) r[tid] = m;
+            else if (part == parts - 1 && tid > part && tid < KSPLIT_MAX) r[tid] = 0.0;
+        }
+    }
+}
+
+// The metric tables of a block's cells (two ghosts a side) into LDS, phi cells
+// kt .. kt + nk - 1 (counted with the ghosts); the threads t0 .. of three waves.
+template <int BI, int BJ, int LIM>
+DEV void load_tables(const KArgs &a, const AS_CONST LevelGeo *lg, int org0, int org1, int org2, int kt, int nk, int tid,
+                     LdsR *sR, LdsT *sT, LdsP *sP)
+{
+    if (tid < BI + 4) {
+        const AS_GLOBAL RecR *q = (const AS_GLOBAL RecR *)(uintptr_t)lg->r + org0 + tid;
+        sR[tid] = LdsR{slope_scale<LIM>(q->idm), slope_scale<LIM>(q->idp), q->idc, q->hm, q->hp, q->am, q->ap,
+                       q->rt, q->icfl, q->irc, a.omega * a.omega * q->rc, a.gm * IC_RCP(q->rc * q->rc), 0.0};
+    } else if (tid >= 64 && tid < 64 + BJ + 4) {
+        const AS_GLOBAL RecT *q = (const AS_GLOBAL RecT *)(uintptr_t)lg->t + org1 + tid - 64;
+        sT[tid - 64] = LdsT{slope_scale<LIM>(q->idm), slope_scale<LIM>(q->idp), q->idc, q->hm, q->hp, q->thm, q->thp,
+                            q->ctil, q->sinc, q->cosc, q->phf, q->icfl, q->isinc, 2.0 * a.omega * q->sinc,
+                            2.0 * a.omega * q->cosc};
+    } else if (tid >= 128 && tid < 128 + nk) {
+        const AS_GLOBAL RecP *q = (const AS_GLOBAL RecP *)(uintptr_t)lg->p + org2 + kt + tid - 128;
+        sP[tid - 128] = LdsP{slope_scale<LIM>(q->idm), slope_scale<LIM>(q->idp), q->idc, q->hm, q->hp, q->iw};
+    }
+}
 
 // Which wave does which face passes of a plane.  A pass is one wave's worth of
 // rows (r-faces) or columns (theta-faces); per plane a wave with columns has
@@ -236,7 +324,7 @@ k_stage(KArgs a)
     // column on the odd ones (rows of 21 and differences of 16 doubles cost 38 %
     // of the LDS cycles in bank conflicts)
     constexpr int PI = BI + 4 + ((BI + 4) % 4 == 2 ? 0 : 2), PJ = BJ + 4;
-    constexpr int DI = BI + (BI % 4 == 2 ? 0 : 2);
+    constexpr int DI = tile_pitch(BI);
     static_assert(PI % 4 == 2 && DI % 4 == 2, "LDS row pitch");
     constexpr int NCOL = BI * BJ;
     constexpr int NHALO = 4 * (BI + BJ);
@@ -300,8 +388,8 @@ k_stage(KArgs a)
         unsigned long long hp[2] = {q0.base, q1.base};
         int hv[2] = {8 * q0.sv, 8 * q1.sv}, hk[2] = {0, 0}, hw[2] = {-1, -1};
         {
-            const FaceMap m0 = face_map<S>(a, slot, nb, 0, 0), m1 = face_map<S>(a, slot, nb, 0, 1);
-            const FaceMap m2 = face_map<S>(a, slot, nb, 1, 0), m3 = face_map<S>(a, slot, nb, 1, 1);
+            const FaceMap m0 = face_map<S>(a, slot, nb.n0, 0, 0), m1 = face_map<S>(a, slot, nb.n1, 0, 1);
+            const FaceMap m2 = face_map<S>(a, slot, nb.n2, 1, 0), m3 = face_map<S>(a, slot, nb.n3, 1, 1);
 #pragma unroll
             for (int h = 0; h < HIT; ++h) {
                 const int t = tid - NCOL + h * NSP;
@@ -340,25 +428,12 @@ k_stage(KArgs a)
         const AS_CONST RecP &pm1 = in_const(lg->p)[org2 + k0 + 1], &p0 = in_const(lg->p)[org2 + k0 + 2];
         __syncthreads();                         // the LDS of the item before is done with
         // the metric tables (read after the barrier that ends the prologue)
-        if (tid < BI + 4) {
-            const AS_GLOBAL RecR *q = (const AS_GLOBAL RecR *)(uintptr_t)lg->r + org0 + tid;
-            sR[tid] = LdsR{slope_scale<LIM>(q->idm), slope_scale<LIM>(q->idp), q->idc, q->hm, q->hp, q->am, q->ap,
-                           q->rt, q->icfl, q->irc, a.omega * a.omega * q->rc, a.gm * IC_RCP(q->rc * q->rc), 0.0};
-        } else if (tid >= 64 && tid < 64 + BJ + 4) {
-            const AS_GLOBAL RecT *q = (const AS_GLOBAL RecT *)(uintptr_t)lg->t + org1 + tid - 64;
-            sT[tid - 64] = LdsT{slope_scale<LIM>(q->idm), slope_scale<LIM>(q->idp), q->idc, q->hm, q->hp, q->thm, q->thp,
-                                q->ctil, q->sinc, q->cosc, q->phf, q->icfl, q->isinc, 2.0 * a.omega * q->sinc,
-                                2.0 * a.omega * q->cosc};
-        } else if (tid >= 128 && tid < 128 + BK + 4) {
-            const AS_GLOBAL RecP *q = (const AS_GLOBAL RecP *)(uintptr_t)lg->p + org2 + tid - 128;
-            sP[tid - 128] = LdsP{slope_scale<LIM>(q->idm), slope_scale<LIM>(q->idp), q->idc, q->hm, q->hp, q->iw};
-        }
+        load_tables<BI, BJ, LIM>(a, lg, org0, org1, org2, 0, BK + 4, tid, sR, sT, sP);
         // phi-face k0-1/2; registers carried along k: wL = face state of cell k
         // at k+1/2, Fm = flux at k-1/2; W(k) and W(k+1) of the own column sit in
         // LDS
         double wL[NV], Fm[NV];
-        int badc = -1;                           // first non-physical input (or stage-2 output) cell of this column
-        int nfr = 0, nfp = 0;                    // cells of this column the density / pressure floor acted on
+        CellLog log;
         double *const W0 = &sW[0][0][0][0], *const D0 = &sD[0][0][0][0];
         constexpr int WV = PJ * PI, WB = NV * WV, DV = BJ * DI, DB = NV * DV;     // LDS strides per variable and plane
         int cw = (cj + 2) * PI + ci + 2, cd = cj * DI + ci;
@@ -407,7 +482,6 @@ k_stage(KArgs a)
         asm volatile("" : "+v"(rc), "+v"(tc), "+v"(rjl), "+v"(til), "+v"(cw), "+v"(cd), "+v"(crf));
         const unsigned long long ubase = (uintptr_t)(a.Ubase + (size_t)slot * NV * S::NC);
         const unsigned long long uout = (uintptr_t)(a.Uout + (size_t)slot * NV * S::NC);
-        double rmax = 0.0;
 
         // What a thread needs from memory in the planes ahead is asked for early,
         // into registers.  A: the column's plane k+2 for the phi-face of plane k,
@@ -455,40 +529,16 @@ k_stage(KArgs a)
                     Wc[cw + v * WV] = W2[v];         // own cell of plane kc+2, where plane kc's was
                     Dc[cd + v * DV] = 0.0;
                 }
-                if (badc < 0 && unphysical<NV>(w)) badc = tid + NCOL * kc;
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
-                    acc[v] = acc[v] - kf * (Fp[v] - Fm[v]);
+                    acc[v] = acc[v] + fma(-kf, Fp[v], kf * Fm[v]);
                     Fm[v] = Fp[v];
                 }
-                if (!a.cart) {
-                    const double c = rr.om2r * tt.sinc;
-                    add_sources(w, rt, tt.ctil, tt.s2, tt.c2, fma(c, tt.sinc, -rr.gg), c * tt.cosc, acc);
-                }
+                update_cell<NV>(a, gs, rr, tt, iw, adt, crf || (kc == 0 && (mk & 16)) || (kc == BK - 1 && (mk & 32)),
+                                tid + NCOL * kc, w, acc, B, log);
                 const unsigned long long uo = uout + 8ll * kc * NCOL;
-                double unew[NV];
 #pragma unroll
-                for (int v = 0; v < NV; ++v) unew[v] = B[v] + adt * acc[v];
-                // floors now, or after the reflux for cells on a coarse-fine face
-                const bool rf_cell = crf || (kc == 0 && (mk & 16)) || (kc == BK - 1 && (mk & 32));
-                if (!rf_cell) {
-                    cons_to_prim<false, NV>(unew, w, gs);
-                    if (unew[0] < a.rho_floor || w[4] < a.p_floor) {         // rare
-                        const int f = apply_floors(unew, gs, a.rho_floor, a.p_floor);
-                        nfr += f & 1;
-                        nfp += f >> 1;
-                        cons_to_prim<false, NV>(unew, w, gs);
-                    }
-                }
-#pragma unroll
-                for (int v = 0; v < NV; ++v) st_at(uo, v * S::NC, tb, unew[v]);
-                if (a.want_rate && !rf_cell) {       // refluxed cells: after the reflux
-                    // the step's result: a non-finite value created in this stage
-                    // would otherwise drop out of the CFL maximum unnoticed
-                    if (badc < 0 && unphysical<NV>(w)) badc = tid + NCOL * kc;
-                    const double rate = cell_rate_of(w, rr.icfl, rr.irc * tt.icfl, rr.irc * tt.isinc * iw, gs);
-                    rmax = rate > rmax ? rate : rmax;
-                }
+                for (int v = 0; v < NV; ++v) st_at(uo, v * S::NC, tb, B[v]);
             }
             if (k == k1) break;
             double *const Wk = W0 + (k & 1) * WB, *const Wk1 = W0 + (~k & 1) * WB, *const Dk = D0 + (k & 1) * DB;
@@ -597,17 +647,170 @@ k_stage(KArgs a)
             if (k + 1 < k1) load_A(k + 1);
             __syncthreads();
         }
-        if (col && badc >= 0 && atomicCAS(&a.bad[2 * mem], 0, slot + 1) == 0) a.bad[2 * mem + 1] = badc;
-        if (col && (nfr | nfp)) {
-            atomicAdd(&a.floors[2 * mem], (unsigned long long)nfr);
-            atomicAdd(&a.floors[2 * mem + 1], (unsigned long long)nfp);
+        end_item<NT>(a, slot, mem, part, ks, log, sred);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// the same stage for short work lists
+// ---------------------------------------------------------------------------
+// k_stage marches: a work-group does the planes of its part one after another,
+// which costs latency where the list does not fill the chip.  k_tile does KZ
+// planes of a block at once, with the same face states, fluxes and sums, hence
+// the same bits: the rows of cells along r and theta, then along phi, are
+// passes of one wave each, straight from memory (64 / (B + 4) rows a wave, halo
+// cells included, neighbours passed between lanes); the differences are added
+// in LDS, the phi ones behind a barrier, and after another one every thread
+// updates cells.  It executes about 1.3 times the instructions (the phi rows of
+// KZ cells carry four halo cells), but no wave waits for another's plane, and
+// four waves a SIMD (128 VGPRs) hide each other's latency.
+
+// Measured (stage launch, k_stage with its default schedule / k_tile): 8 blocks
+// of 12^3 21.5 / 14.8 us, 40 of them 25 / 20, 80 31 / 26, 160 45 / 40, 320 71 /
+// 69, 512 84 / 97; 1,024 blocks of 4^3 42 / 24; 48 of 16 x 12 x 12 27 / 29.
+constexpr int TT = 512;      // threads per work-group of k_tile
+
+// Rows along D of planes k0 .. k0 + KZ - 1, and how many go into a pass.
+template <int BI, int BJ, int KZ, int D>
+struct TileRows {
+    static constexpr int B = D == 0 ? BI : D == 1 ? BJ : KZ;                 // cells of a row
+    static constexpr int X = D == 0 ? BJ : D == 1 ? BI : BI * BJ;            // rows per plane (phi: in all)
+    static constexpr int RL = B + 4, RPW = 64 / RL, NROW = D == 2 ? X : X * KZ, NP = (NROW + RPW - 1) / RPW;
+};
+
+// Passes first, first + step, ... over the rows along D.
+template <int BI, int BJ, int BK, int NV, int LIM, int KZ, int D>
+DEV void tile_passes(const KArgs &a, int slot, int nlo, int nhi, int flo, int fhi, const Gas &gs, int k0, int first,
+                     int step, int lane, const LdsR *sR, const LdsT *sT, const LdsP *sP, double *D0)
+{
+    using S = Shape<BI, BJ, BK, NV>;
+    using T = TileRows<BI, BJ, KZ, D>;
+    constexpr int PL = BI * BJ, DI = tile_pitch(BI), DK = BJ * DI + 2, DV = KZ * DK;
+    constexpr int ext = S::dim(D), st = D == 0 ? 1 : D == 1 ? BI : PL;      // the block along D: cells, stride
+    const unsigned long long own = (uintptr_t)(a.U + (size_t)slot * NV * S::NC);
+    const FaceMap mlo = face_map<S>(a, slot, nlo, D, 0), mhi = face_map<S>(a, slot, nhi, D, 1);
+    const int c = lane % T::RL - 2, rl = lane < T::RPW * T::RL ? lane / T::RL : T::NROW;
+    const int cd = D == 2 ? k0 + c : c;
+    // the lane's cell: in the block, or behind its lower or upper face
+    const bool below = cd < 0, above = cd >= ext;
+    const unsigned long long base = below ? (uintptr_t)mlo.base : above ? (uintptr_t)mhi.base : own;
+    const int off = below ? (cd + 2) * mlo.sl : above ? (cd - ext) * mhi.sl : st * cd;
+    const int sx = D == 2 ? 1 : below ? mlo.sa : above ? mhi.sa : D == 0 ? BI : 1;
+    const int sk = D == 2 ? 0 : below ? mlo.sk : above ? mhi.sk : PL;
+    const long long sv = 8 * (below ? mlo.sv : above ? mhi.sv : S::NC);
+#pragma unroll 1
+    for (int p = first; p < T::NP; p += step) {
+        const int row = p * T::RPW + rl;
+        const bool act = row < T::NROW;
+        const int x = act ? row % T::X : 0, kk = act ? row / T::X : 0;
+        unsigned long long ad = base + 8ll * (off + x * sx + (k0 + kk) * sk);
+        double u[NV], w[NV], wm[NV], wp[NV], lo[NV], hi[NV], fx[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v, ad += sv) u[v] = *(const AS_GLOBAL double *)ad;
+        cons_to_prim<false, NV>(u, w, gs);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            wm[v] = shr1(w[v]);
+            wp[v] = shl1(w[v]);
         }
-        if (a.want_rate) {
-            // this part's CFL maximum; the last part clears the unused entries
-            const double m = block_max(col ? rmax : 0.0, sred);
-            if (tid == 0) a.rate[(size_t)slot * KSPLIT_MAX + part] = m;
-            if (part == ks - 1 && tid > part && tid < KSPLIT_MAX) a.rate[(size_t)slot * KSPLIT_MAX + tid] = 0.0;
+        double fm, fp;
+        if (D == 0) {
+            const LdsR &m = sR[c + 2];
+            reconstruct<LIM, NV>(wm, w, wp, m.im, m.ip, m.ic, m.hm, m.hp, lo, hi);
+            fm = m.am;
+            fp = m.ap;
+        } else if (D == 1) {
+            const LdsT &m = sT[c + 2];
+            reconstruct<LIM, NV>(wm, w, wp, m.im, m.ip, m.ic, m.hm, m.hp, lo, hi);
+            const double rt = sR[x + 2].rt;
+            fm = rt * m.thm;
+            fp = rt * m.thp;
+        } else {
+            const LdsP &m = sP[c + 2];
+            reconstruct<LIM, NV>(wm, w, wp, m.im, m.ip, m.ic, m.hm, m.hp, lo, hi);
+            fm = fp = sR[x % BI + 2].rt * sT[x / BI + 2].phf * m.iw;
         }
+#pragma unroll
+        for (int v = 0; v < NV; ++v) hi[v] = shr1(hi[v]);
+        rusanov<D, NV>(hi, lo, fx, gs);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) lo[v] = fma(-fp, shl1(fx[v]), fm * fx[v]);
+        if (act && c >= 0 && c < T::B) {
+            double *const d = D0 + (D == 0 ? kk * DK + x * DI + c : D == 1 ? kk * DK + c * DI + x : c * DK + x / BI * DI + x % BI);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) lds_add(d + v * DV, lo[v]);
+        }
+        // raw flux at a coarse-fine face of the block, for the reflux
+        if (act && (cd == 0 || cd == ext) && c >= 0 && c <= T::B) {
+            const int r = cd == 0 ? flo : fhi;
+            if (r >= 0) {
+                constexpr int FB = D == 2 ? 1 : BK;
+                double *const f = a.freg + (size_t)r * a.reg_stride + (D == 2 ? x : (k0 + kk) * T::X + x);
+                for (int v = 0; v < NV; ++v) f[v * T::X * FB] = fx[v];
+            }
+        }
+    }
+}
+
+template <int BI, int BJ, int BK, int NV, int LIM, int KZ>
+__global__ void __launch_bounds__(TT) __attribute__((amdgpu_waves_per_eu(4, 4)))
+k_tile(KArgs a)
+{
+    using S = Shape<BI, BJ, BK, NV>;
+    static_assert(BK % KZ == 0 && BK / KZ <= KSPLIT_MAX, "planes per work-group");
+    constexpr int PL = BI * BJ, DI = tile_pitch(BI), DK = BJ * DI + 2, DV = KZ * DK, PARTS = BK / KZ, NW = TT / 64;
+    __shared__ double sD[NV * DV];
+    __shared__ LdsR sR[BI + 4];
+    __shared__ LdsT sT[BJ + 4];
+    __shared__ LdsP sP[KZ + 4];
+    __shared__ double sred[NW];
+    const Gas gs = a.gas;
+    const int nwork = *in_const(a.nitems) * PARTS;
+    for (int wi = blockIdx.x; wi < nwork; wi += gridDim.x) {
+        const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int it = wi / PARTS, part = wi % PARTS, k0 = part * KZ;
+        const int slot = in_const(a.items)[it];
+        const AS_CONST BlockDesc *const bd = in_const(a.desc) + slot;
+        const int mem = bd->member, mk = bd->reflux_mask;
+        const double dt = in_const(a.dt)[mem];
+        if (dt <= 0.0) continue;                 // member finished: state stays in place
+        const double adt = a.alpha * dt;
+        const AS_CONST LevelGeo *const lg = in_const(a.geo) + bd->level;
+        __syncthreads();                         // the LDS of the item before is done with
+        load_tables<BI, BJ, LIM>(a, lg, bd->org[0], bd->org[1], bd->org[2], k0, KZ + 4, tid, sR, sT, sP);
+        for (int q = tid; q < NV * DV; q += TT) sD[q] = 0.0;
+        __syncthreads();
+        tile_passes<BI, BJ, BK, NV, LIM, KZ, 0>(a, slot, bd->nbr[0], bd->nbr[1], bd->freg[0], bd->freg[1], gs, k0, wave, NW,
+                                                lane, sR, sT, sP, sD);
+        // the theta passes go on where the r passes ended among the waves
+        tile_passes<BI, BJ, BK, NV, LIM, KZ, 1>(a, slot, bd->nbr[2], bd->nbr[3], bd->freg[2], bd->freg[3], gs, k0,
+                                                (wave + NW - TileRows<BI, BJ, KZ, 0>::NP % NW) % NW, NW, lane, sR, sT, sP, sD);
+        __syncthreads();
+        tile_passes<BI, BJ, BK, NV, LIM, KZ, 2>(a, slot, bd->nbr[4], bd->nbr[5], bd->freg[4], bd->freg[5], gs, k0, wave, NW,
+                                                lane, sR, sT, sP, sD);
+        __syncthreads();
+        CellLog log;
+        const unsigned long long own = (uintptr_t)(a.U + (size_t)slot * NV * S::NC + (size_t)k0 * PL);
+        const unsigned long long ubase = (uintptr_t)(a.Ubase + (size_t)slot * NV * S::NC + (size_t)k0 * PL);
+        const unsigned long long uout = (uintptr_t)(a.Uout + (size_t)slot * NV * S::NC + (size_t)k0 * PL);
+#pragma unroll 1
+        for (int q = tid; q < PL * KZ; q += TT) {
+            const int i = q % BI, j = q / BI % BJ, kk = q / PL, k = k0 + kk;
+            double u[NV], w[NV], acc[NV];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) u[v] = ld_at(own, v * S::NC, 8u * q);
+            cons_to_prim<false, NV>(u, w, gs);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) u[v] = ld_at(ubase, v * S::NC, 8u * q);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) acc[v] = sD[kk * DK + j * DI + i + v * DV];
+            const bool refluxed = (i == 0 && (mk & 1)) || (i == BI - 1 && (mk & 2)) || (j == 0 && (mk & 4)) ||
+                                  (j == BJ - 1 && (mk & 8)) || (k == 0 && (mk & 16)) || (k == BK - 1 && (mk & 32));
+            update_cell<NV>(a, gs, sR[i + 2], sT[j + 2], sP[kk + 2].iw, adt, refluxed, q + k0 * PL, w, acc, u, log);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) st_at(uout, v * S::NC, 8u * q, u[v]);
+        }
+        end_item<TT>(a, slot, mem, part, PARTS, log, sred);
     }
 }
 
@@ -635,7 +838,25 @@ void launch_stage(dim3 g, hipStream_t s, const KArgs &a, int waves, int limiter)
     }
 }
 
+// kz planes of a block per work-group: 1, 2 or 4
+template <int BI, int BJ, int BK, int NV, int LIM>
+void launch_tile_lim(dim3 g, hipStream_t s, const KArgs &a, int kz)
+{
+    if (kz == 1) hipLaunchKernelGGL((k_tile<BI, BJ, BK, NV, LIM, 1>), g, dim3(TT), 0, s, a);
+    else if (kz == 2) hipLaunchKernelGGL((k_tile<BI, BJ, BK, NV, LIM, 2>), g, dim3(TT), 0, s, a);
+    else hipLaunchKernelGGL((k_tile<BI, BJ, BK, NV, LIM, 4>), g, dim3(TT), 0, s, a);
+}
+template <int BI, int BJ, int BK, int NV>
+void launch_tile(dim3 g, hipStream_t s, const KArgs &a, int kz, int limiter)
+{
+    if (limiter == LIM_MINMOD) launch_tile_lim<BI, BJ, BK, NV, LIM_MINMOD>(g, s, a, kz);
+    else if (limiter == LIM_VANLEER) launch_tile_lim<BI, BJ, BK, NV, LIM_VANLEER>(g, s, a, kz);
+    else launch_tile_lim<BI, BJ, BK, NV, LIM_MC>(g, s, a, kz);
+}
+
 #define IC_INSTANTIATE(BI, BJ, BK)                                                                  \
+    template void launch_tile<BI, BJ, BK, 8>(dim3, hipStream_t, const KArgs &, int, int);          \
+    template void launch_tile<BI, BJ, BK, 9>(dim3, hipStream_t, const KArgs &, int, int);          \
     template __global__ void k_stage<BI, BJ, BK, 8, 1, LIM_MC>(KArgs);                             \
     template __global__ void k_stage<BI, BJ, BK, 8, 2, LIM_MC>(KArgs);                             \
     template __global__ void k_stage<BI, BJ, BK, 8, 2, LIM_MINMOD>(KArgs);                         \
