@@ -388,15 +388,14 @@ ic_status ic_mlp_infer(const float *raw, long n, const float *params, const floa
  * probabilities of ic_mlp_infer with every array on the device and no
  * allocation of any kind.  raw_dev [n x 512], params_dev [IC_MLP_NPARAM],
  * mean_dev and std_dev [512] (std must be positive; the values are not
- * checked on the host), prob_dev [n]: device pointers owned by the caller.
+ * checked on the host), prob_dev [n], which overlaps none of them: device
+ * pointers owned by the caller.
  * The work is enqueued on hip_stream (NULL = the null stream) and the call
  * returns without synchronising; prob_dev is valid once the stream has
- * completed it.  Intermediate values live in a fixed device scratch of the
- * library (one copy per device, about 6.2 MiB, held until the process
- * ends), so n may not exceed IC_MLP_NOALLOC_ROWS (IC_E_INVALID).  Every call
- * on a device shares that scratch: calls that overlap on one device (other
- * streams, other threads) race and must be ordered by the caller.  Results
- * equal ic_mlp_infer's bit for bit. */
+ * completed it.  n may not exceed IC_MLP_NOALLOC_ROWS (IC_E_INVALID).  One
+ * kernel launch; calls share no memory of the library, so calls on other
+ * streams or threads may overlap.  Results equal ic_mlp_infer's bit for
+ * bit. */
 #define IC_MLP_NOALLOC_ROWS 4096
 ic_status ic_mlp_infer_noalloc(const float *raw_dev, long n, const float *params_dev, const float *mean_dev,
                                const float *std_dev, float *prob_dev, void *hip_stream);
@@ -471,9 +470,8 @@ int ic_pool_capacity(const ic_sim *sim);
  * hipFree.  alloc must return memory of the current device aligned to at
  * least 256 bytes, or NULL (the allocating call then fails with IC_E_NOMEM).
  * Every buffer goes back through the allocator it came from, also after a
- * later change.  Pinned host memory and the static scratch of
- * ic_mlp_infer_noalloc are not affected.  Process-wide: do not call it while
- * another thread is inside the library.  IC_E_INVALID if exactly one of alloc
+ * later change.  Pinned host memory is not affected.  Process-wide: do not
+ * call it while another thread is inside the library.  IC_E_INVALID if exactly one of alloc
  * and release is NULL. */
 typedef void *(*ic_alloc_fn)(size_t bytes, void *user);
 typedef void (*ic_free_fn)(void *ptr, void *user);

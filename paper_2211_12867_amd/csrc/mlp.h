@@ -33,11 +33,9 @@ struct MlpHparams {
 // device copy of a trained network for inference inside a sim
 struct MlpDevice {
     float *w = nullptr;       // fp32 parameters
-    uint16_t *wb = nullptr;   // bf16 copies
     float *mean = nullptr, *istd = nullptr;
-    uint16_t *xb = nullptr, *h1 = nullptr, *h2 = nullptr;
+    uint16_t *xb = nullptr;   // normalised inputs, bf16
     float *prob = nullptr;
-    int8_t *flags_tmp = nullptr;
     int cap = 0;
     bool ready = false;
     MlpDevice();
@@ -56,12 +54,10 @@ void mlp_train(const float *raw, const uint8_t *y, long n, const MlpHparams &hp,
                float *std_out, float *loss_epochs);
 void mlp_infer(const float *raw, long n, const float *params, const float *mean, const float *std, float *prob);
 
-// rows of one allocation-free inference call (the fixed device scratch holds
-// their bf16 inputs and hidden layers)
+// rows of one allocation-free inference call
 #ifndef IC_MLP_NOALLOC_ROWS
 #define IC_MLP_NOALLOC_ROWS 4096
 #endif
-// Inference on device arrays with no allocation: scratch is a file-scope
-// device array of mlp.hip, shared by every call on a device.  Enqueued on s.
+// Inference on device arrays with no allocation and no scratch.  Enqueued on s.
 void mlp_infer_noalloc(const float *raw, long n, const float *params, const float *mean, const float *std,
                        float *prob, hipStream_t s);

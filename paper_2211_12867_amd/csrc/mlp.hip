@@ -16,9 +16,9 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <mutex>
 #include <stdexcept>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "devmem.h"
@@ -249,6 +249,147 @@ __global__ void k_head(const uint16_t *H2, const uint16_t *w3, const float *b3, 
     }
 }
 
+// ---------------------------------------------------------------------------
+// inference in one launch: z-score, bf16 rounding of inputs and weights, both
+// layers, head.  Bound by latency and by the 320 KB of fp32 weights each
+// work-group reads from the L2 (2.2 us at 64 B/clock), so the two layers share
+// one launch and the weights are asked for all at once, up to 160 loads a lane
+// in flight, and stay in registers as MFMA operands for every 16-row tile the
+// group takes.  Eight waves: wave w owns columns 16 w .. 16 w + 15 of both
+// layers, so a row tile is 16 + 4 MFMA steps a wave, the k-steps of 32 in
+// ascending order and the head's 128 products in column order (the rounding
+// points and orders of the training pass).  Raw inputs, calls queued one after
+// another: 1 row 22.8 -> 8.0 us, 677 rows 30.3 -> 7.9, 4,096 rows 34.1 -> 8.4
+// against six launches (1/std, weights to bf16, z-score, two GEMMs, head).
+// ---------------------------------------------------------------------------
+constexpr int NET_TH = 512;                // threads: eight waves of 16 columns
+constexpr int NET_XP = IC_MLP_IN + 8;      // padded LDS rows, bf16
+constexpr int NET_HP = IC_MLP_HID + 8;
+
+// two fp32 values as bf16 (nearest even, as f2bf), packed
+DEV_EPI uint32_t f2bf2(float lo, float hi)
+{
+    uint32_t a = __float_as_uint(lo), b = __float_as_uint(hi);
+    a += 0x7FFFu + ((a >> 16) & 1u);
+    b += 0x7FFFu + ((b >> 16) & 1u);
+    return __builtin_amdgcn_perm(b, a, 0x07060302u);
+}
+
+DEV_EPI bf16x8_t pack8(const float *v)
+{
+    const uint4 q = make_uint4(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]), f2bf2(v[4], v[5]), f2bf2(v[6], v[7]));
+    return __builtin_bit_cast(bf16x8_t, q);
+}
+
+// B operands of NK MFMA steps from the fp32 weights W[k][128]: lane l holds
+// column n = 16 wave + l % 16 and k = 32 step + 8 (l / 16) + 0..7
+template <int NK>
+DEV_EPI void weights_ask(const float *W, int wave, int lane, float (*v)[8])
+{
+    const float *q = W + (lane >> 4) * 8 * IC_MLP_HID + wave * 16 + (lane & 15);
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[kk][e] = q[(kk * 32 + e) * IC_MLP_HID];
+}
+
+// C rows 4 (l / 16) + 0..3, column l % 16 of a 16-row tile of L (rows of
+// `pitch` bf16) times the NK operands b
+template <int NK>
+DEV_EPI float4_t tile_mfma(const uint16_t *L, int pitch, int lane, const bf16x8_t *b)
+{
+    float4_t acc{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) {
+        const bf16x8_t a = *(const bf16x8_t *)&L[(lane & 15) * pitch + kk * 32 + (lane >> 4) * 8];
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[kk], acc, 0, 0, 0);
+    }
+    return acc;
+}
+
+DEV_EPI float relu(float v) { return v > 0.f ? v : 0.f; }
+
+// logit of a row: sum_j H2[j] w3[j] + b3 (fp32, j ascending), w3 rounded to bf16
+DEV_EPI float head_row(const uint16_t *H2, const float *w3, float b3)
+{
+    float s = 0.f;
+#pragma unroll 16
+    for (int j = 0; j < IC_MLP_HID; ++j) s += bf2f(H2[j]) * w3[j];
+    return s + b3;
+}
+
+// RAW: x is fp32 raw inputs, z-scored here with mean and std; else bf16, normalised
+template <bool RAW>
+__global__ void __launch_bounds__(NET_TH) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_infer(const void *x, const float *mean, const float *std, const float *P, int n, float *prob)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t Xs[16 * NET_XP];
+    __shared__ __attribute__((aligned(16))) uint16_t Hs[16 * NET_HP];
+    __shared__ __attribute__((aligned(16))) uint16_t Gs[16 * NET_HP];
+    __shared__ __attribute__((aligned(16))) float w3s[IC_MLP_HID];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int col = wave * 16 + (lane & 15), row4 = (lane >> 4) * 4;
+    const int ntile = (n + 15) / 16;
+    // a thread's share of a tile's inputs: RAW one column of 16 rows (any
+    // alignment of the caller's array), else two 16-byte pieces
+    constexpr int NX = RAW ? 16 : 2;
+    using XT = typename std::conditional<RAW, float, uint4>::type;
+    XT xr[NX];
+    auto ask = [&](int tile) {
+#pragma unroll
+        for (int e = 0; e < NX; ++e) {
+            if constexpr (RAW) {
+                const int b = tile * 16 + e;
+                xr[e] = b < n ? ((const float *)x)[(long)b * IC_MLP_IN + tid] : 0.f;
+            } else {
+                const int b = tile * 16 + e * 8 + (tid >> 6);
+                xr[e] = b < n ? ((const uint4 *)x)[(long)b * (IC_MLP_IN / 8) + lane] : make_uint4(0u, 0u, 0u, 0u);
+            }
+        }
+    };
+    int tile = blockIdx.x;
+    ask(tile);
+    float mu = 0.f, is = 1.f;
+    if constexpr (RAW) {
+        mu = mean[tid];
+        is = 1.0f / std[tid];
+    }
+    float v1[16][8], v2[4][8];
+    weights_ask<16>(P + IC_MLP_OFF_W1, wave, lane, v1);
+    weights_ask<4>(P + IC_MLP_OFF_W2, wave, lane, v2);
+    const float b1 = P[IC_MLP_OFF_B1 + col], b2 = P[IC_MLP_OFF_B2 + col], b3 = P[IC_MLP_OFF_B3];
+    if (tid < IC_MLP_HID) w3s[tid] = bf2f(f2bf(P[IC_MLP_OFF_W3 + tid]));
+    bf16x8_t w1[16], w2[4];
+#pragma unroll
+    for (int kk = 0; kk < 16; ++kk) w1[kk] = pack8(v1[kk]);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) w2[kk] = pack8(v2[kk]);
+    for (; tile < ntile; tile += gridDim.x) {
+#pragma unroll
+        for (int e = 0; e < NX; ++e) {
+            if constexpr (RAW)
+                Xs[e * NET_XP + tid] = f2bf((xr[e] - mu) * is);
+            else
+                *(uint4 *)&Xs[(e * 8 + (tid >> 6)) * NET_XP + lane * 8] = xr[e];
+        }
+        __syncthreads();
+        if (tile + (int)gridDim.x < ntile) ask(tile + gridDim.x);
+        const float4_t z1 = tile_mfma<16>(Xs, NET_XP, lane, w1);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) Hs[(row4 + t) * NET_HP + col] = f2bf(relu(z1[t] + b1));
+        __syncthreads();
+        const float4_t z2 = tile_mfma<4>(Hs, NET_HP, lane, w2);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) Gs[(row4 + t) * NET_HP + col] = f2bf(relu(z2[t] + b2));
+        __syncthreads();
+        // Gs is written again two barriers on, Xs was last read one barrier ago
+        if (tid < 16 && tile * 16 + tid < n) {
+            const float s = head_row(&Gs[tid * NET_HP], w3s, b3);
+            prob[tile * 16 + tid] = 1.f / (1.f + expf(-s));
+        }
+    }
+}
+
 // dZ2 = dz w3 [H2 > 0] (fp32 and bf16 copies)
 __global__ void k_back2(const float *dz, const uint16_t *w3, const uint16_t *H2, int n, float *dZ2, uint16_t *dZ2b)
 {
@@ -340,13 +481,6 @@ __global__ void k_normalise(const float *raw, const float *mean, const float *is
     xb[q] = f2bf((raw[q] - mean[f]) * istd[f]);
 }
 
-// 1 / std per input (fp32 division, correctly rounded as on the host)
-__global__ void k_istd(const float *std, float *istd)
-{
-    const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    if (f < IC_MLP_IN) istd[f] = 1.0f / std[f];
-}
-
 // minibatch gather: rows order[b0 + q] of the normalised inputs and labels
 __global__ void k_gather(const uint16_t *xall, const uint8_t *yall, const long *order, long b0, int B, uint16_t *xb,
                          uint8_t *yb)
@@ -430,19 +564,16 @@ MlpDevice::MlpDevice() = default;
 
 MlpDevice::~MlpDevice()
 {
-    for (void *q : {(void *)w, (void *)wb, (void *)mean, (void *)istd, (void *)xb, (void *)h1, (void *)h2,
-                    (void *)prob, (void *)flags_tmp})
-        dev_free(q);
+    for (void *q : {(void *)w, (void *)mean, (void *)istd, (void *)xb, (void *)prob}) dev_free(q);
 }
 
 void MlpDevice::set(const float *params, const float *mean_h, const float *std_h)
 {
     if (!w) {
         w = (float *)dev_malloc(IC_MLP_NPARAM * sizeof(float));
-        wb = (uint16_t *)dev_malloc(IC_MLP_NPARAM * sizeof(uint16_t));
         mean = (float *)dev_malloc(IC_MLP_IN * sizeof(float));
         istd = (float *)dev_malloc(IC_MLP_IN * sizeof(float));
-        if (!w || !wb || !mean || !istd) throw std::runtime_error("device allocation failed");
+        if (!w || !mean || !istd) throw std::runtime_error("device allocation failed");
     }
     std::vector<float> is(IC_MLP_IN);
     for (int f = 0; f < IC_MLP_IN; ++f) is[f] = 1.0f / std_h[f];
@@ -450,7 +581,6 @@ void MlpDevice::set(const float *params, const float *mean_h, const float *std_h
         hipMemcpy(mean, mean_h, IC_MLP_IN * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(istd, is.data(), IC_MLP_IN * sizeof(float), hipMemcpyHostToDevice) != hipSuccess)
         throw std::runtime_error("hipMemcpy failed");
-    hipLaunchKernelGGL(k_to_bf16, dim3((IC_MLP_NPARAM + 255) / 256), dim3(256), 0, 0, w, wb, (long)IC_MLP_NPARAM);
     if (hipDeviceSynchronize() != hipSuccess) throw std::runtime_error("device error");
     ready = true;
 }
@@ -458,27 +588,25 @@ void MlpDevice::set(const float *params, const float *mean_h, const float *std_h
 void MlpDevice::reserve(int n)
 {
     if (n <= cap) return;
-    for (void *q : {(void *)xb, (void *)h1, (void *)h2, (void *)prob}) dev_free(q);
-    xb = h1 = h2 = nullptr;
+    for (void *q : {(void *)xb, (void *)prob}) dev_free(q);
+    xb = nullptr;
     prob = nullptr;
     cap = n + n / 2 + 64;
     xb = (uint16_t *)dev_malloc((size_t)cap * IC_MLP_IN * sizeof(uint16_t));
-    h1 = (uint16_t *)dev_malloc((size_t)cap * IC_MLP_HID * sizeof(uint16_t));
-    h2 = (uint16_t *)dev_malloc((size_t)cap * IC_MLP_HID * sizeof(uint16_t));
     prob = (float *)dev_malloc((size_t)cap * sizeof(float));
-    if (!xb || !h1 || !h2 || !prob) throw std::runtime_error("device allocation failed");
+    if (!xb || !prob) throw std::runtime_error("device allocation failed");
 }
+
+// One work-group per 16-row tile up to one per compute unit: beyond that a
+// group takes several tiles with the weights it holds, which saves their
+// 320 KB a tile.
+static dim3 infer_grid(long n) { return dim3((unsigned)std::min((n + 15) / 16, 256L)); }
 
 // forward pass over n rows of xb (already filled) -> prob
 void MlpDevice::forward(hipStream_t s, int n)
 {
-    const uint16_t *W1 = wb + IC_MLP_OFF_W1, *W2 = wb + IC_MLP_OFF_W2, *w3 = wb + IC_MLP_OFF_W3;
-    gemm(s, xb, IC_MLP_IN, 1, W1, IC_MLP_HID, 1, n, IC_MLP_HID, IC_MLP_IN, w + IC_MLP_OFF_B1, 1, nullptr, h1,
-         IC_MLP_HID);
-    gemm(s, h1, IC_MLP_HID, 1, W2, IC_MLP_HID, 1, n, IC_MLP_HID, IC_MLP_HID, w + IC_MLP_OFF_B2, 1, nullptr, h2,
-         IC_MLP_HID);
-    hipLaunchKernelGGL(k_head, dim3((n + 255) / 256), dim3(256), 0, s, h2, w3, w + IC_MLP_OFF_B3, n,
-                       (const uint8_t *)nullptr, 0.f, (float *)nullptr, prob, (float *)nullptr, (float *)nullptr);
+    hipLaunchKernelGGL((k_infer<false>), infer_grid(n), dim3(NET_TH), 0, s, (const void *)xb, (const float *)nullptr,
+                       (const float *)nullptr, (const float *)w, n, prob);
 }
 
 void mlp_features(hipStream_t s, const KArgs &a, int bi, int bj, int bk, const int *items,
@@ -673,71 +801,16 @@ void mlp_infer(const float *raw, long n, const float *params, const float *mean,
 }
 
 // ---------------------------------------------------------------------------
-// inference without allocation
+// inference without allocation: the one launch reads the caller's arrays and
+// writes the probabilities, with no intermediate value in device memory
 // ---------------------------------------------------------------------------
-// The scratch of the allocation-free entry point: bf16 weights, 1/std, and
-// the bf16 inputs and both hidden layers of up to IC_MLP_NOALLOC_ROWS rows
-// (6.2 MiB), one copy per device for the life of the process.  Host code
-// reaches it only through the address hipGetSymbolAddress returns for the
-// current device (the array's name is a host-side stand-in).
-namespace {
-constexpr size_t na_align(size_t b) { return (b + 255) / 256 * 256; }
-constexpr size_t kNaWb = 0;
-constexpr size_t kNaIstd = kNaWb + na_align((size_t)IC_MLP_NPARAM * sizeof(uint16_t));
-constexpr size_t kNaX = kNaIstd + na_align((size_t)IC_MLP_IN * sizeof(float));
-constexpr size_t kNaH1 = kNaX + (size_t)IC_MLP_NOALLOC_ROWS * IC_MLP_IN * sizeof(uint16_t);
-constexpr size_t kNaH2 = kNaH1 + (size_t)IC_MLP_NOALLOC_ROWS * IC_MLP_HID * sizeof(uint16_t);
-constexpr size_t kNaBytes = kNaH2 + (size_t)IC_MLP_NOALLOC_ROWS * IC_MLP_HID * sizeof(uint16_t);
-}  // namespace
-
-static __device__ __align__(256) unsigned char scratch[kNaBytes];
-
-namespace {
-constexpr int kNaMaxDevices = 64;
-unsigned char *g_na_scratch[kNaMaxDevices];   // device address of each device's copy, once resolved
-std::mutex g_na_mu;
-
-// Device address of the current device's scratch, resolved on the first call
-// on that device.
-unsigned char *noalloc_scratch()
-{
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) throw std::runtime_error("hipGetDevice failed");
-    if (dev < 0 || dev >= kNaMaxDevices) throw std::runtime_error("device index beyond the scratch table");
-    std::lock_guard<std::mutex> lk(g_na_mu);
-    if (!g_na_scratch[dev]) {
-        void *p = nullptr;
-        const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-        if (e != hipSuccess || !p)
-            throw std::runtime_error(std::string("hipGetSymbolAddress(scratch): ") + hipGetErrorString(e));
-        g_na_scratch[dev] = (unsigned char *)p;
-    }
-    return g_na_scratch[dev];
-}
-}  // namespace
-
 void mlp_infer_noalloc(const float *raw, long n, const float *params, const float *mean, const float *std,
                        float *prob, hipStream_t s)
 {
     if (n < 0 || n > IC_MLP_NOALLOC_ROWS) throw std::invalid_argument("row count outside 0 .. IC_MLP_NOALLOC_ROWS");
-    unsigned char *base = noalloc_scratch();
     if (n == 0) return;
-    uint16_t *wb = (uint16_t *)(base + kNaWb);
-    float *istd = (float *)(base + kNaIstd);
-    uint16_t *xb = (uint16_t *)(base + kNaX);
-    uint16_t *h1 = (uint16_t *)(base + kNaH1);
-    uint16_t *h2 = (uint16_t *)(base + kNaH2);
-    // every scratch element read below is written first in this call: nothing to clear
-    hipLaunchKernelGGL(k_istd, dim3((IC_MLP_IN + 255) / 256), dim3(256), 0, s, std, istd);
-    hipLaunchKernelGGL(k_to_bf16, dim3((IC_MLP_NPARAM + 255) / 256), dim3(256), 0, s, params, wb, (long)IC_MLP_NPARAM);
-    hipLaunchKernelGGL(k_normalise, dim3((n * IC_MLP_IN + 255) / 256), dim3(256), 0, s, raw, mean, istd, n, xb);
-    gemm(s, xb, IC_MLP_IN, 1, wb + IC_MLP_OFF_W1, IC_MLP_HID, 1, (int)n, IC_MLP_HID, IC_MLP_IN, params + IC_MLP_OFF_B1,
-         1, nullptr, h1, IC_MLP_HID);
-    gemm(s, h1, IC_MLP_HID, 1, wb + IC_MLP_OFF_W2, IC_MLP_HID, 1, (int)n, IC_MLP_HID, IC_MLP_HID,
-         params + IC_MLP_OFF_B2, 1, nullptr, h2, IC_MLP_HID);
-    hipLaunchKernelGGL(k_head, dim3((n + 255) / 256), dim3(256), 0, s, h2, wb + IC_MLP_OFF_W3, params + IC_MLP_OFF_B3,
-                       (int)n, (const uint8_t *)nullptr, 0.f, (float *)nullptr, prob, (float *)nullptr,
-                       (float *)nullptr);
+    hipLaunchKernelGGL((k_infer<true>), infer_grid(n), dim3(NET_TH), 0, s, (const void *)raw, mean, std, params,
+                       (int)n, prob);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) throw std::runtime_error(std::string("launch failed: ") + hipGetErrorString(e));
 }

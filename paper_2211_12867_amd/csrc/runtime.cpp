@@ -2866,7 +2866,7 @@ ic_status ic_mlp_infer_noalloc(const float *raw_dev, long n, const float *params
             throw Error(IC_E_INVALID, "bad argument");
         if (n > IC_MLP_NOALLOC_ROWS)
             throw Error(IC_E_INVALID, "ic_mlp_infer_noalloc: " + std::to_string(n) + " rows exceed the limit of " +
-                                          std::to_string(IC_MLP_NOALLOC_ROWS) + " (the fixed scratch)");
+                                          std::to_string(IC_MLP_NOALLOC_ROWS));
         try {
             mlp_infer_noalloc(raw_dev, n, params_dev, mean_dev, std_dev, prob_dev, (hipStream_t)hip_stream);
         } catch (const std::invalid_argument &e) {
