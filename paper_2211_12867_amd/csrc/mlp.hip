@@ -27,6 +27,7 @@
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 __device__ inline uint16_t f2bf(float x)
 {
@@ -75,179 +76,6 @@ __global__ void __launch_bounds__(256) k_features(KArgs a, const int *items, con
     }
 }
 
-// ---------------------------------------------------------------------------
-// GEMM: C = A B (+ bias, relu), bf16 operands, fp32 accumulate on gfx950's
-// v_mfma_f32_16x16x32_bf16.  A(m,k) = A[m*sam + k*sak], B(k,n) = B[k*sbk + n*sbn].
-// A work-group of 4 waves computes a 64x64 tile of C, each wave a 32x32
-// quarter as 2x2 MFMA blocks of 16x16.  K advances in MFMA steps of 32 (the
-// order in which they accumulate), staged through LDS four steps (128 k) at
-// a time: As[m][k] and Bt[n][k] with k contiguous, so that a lane's MFMA
-// operand -- row (A) or column (B) l % 16 and eight consecutive k,
-// 8 (l / 16) + 0..7 -- is one 16-byte LDS read (rows padded by 8 bf16 to
-// spread them over the banks).  Each thread moves 16-byte pieces (eight
-// elements along whichever index is contiguous in memory) with one global
-// load each; the next stage's loads are in flight while the MFMAs of the
-// current one run, from the other of two LDS buffers.  The accumulator holds
-// column l % 16 and rows 4 (l / 16) + 0..3 of a block.
-// Split K (gridDim.z > 1, weight gradients with K = the batch rows): each
-// z-slice accumulates its share of the k-steps and writes fp32 partials
-// P[z][m][n]; k_gemm_reduce sums them in slice order (deterministic) and
-// applies the epilogue.
-// ---------------------------------------------------------------------------
-struct GemmArgs {
-    const uint16_t *A;
-    long sam, sak;
-    const uint16_t *B;
-    long sbk, sbn;
-    int M, N, K;
-    const float *bias;
-    int relu;
-    float *Cf;
-    uint16_t *Cb;
-    long ldc;
-    float *P;                 // split-K partials [gridDim.z][M][N] (gridDim.z > 1)
-};
-
-DEV_EPI void gemm_store(const GemmArgs &g, int m, int n, float v)
-{
-    if (g.bias) v += g.bias[n];
-    if (g.relu) v = v > 0.f ? v : 0.f;
-    if (g.Cf) g.Cf[(long)m * g.ldc + n] = v;
-    if (g.Cb) g.Cb[(long)m * g.ldc + n] = f2bf(v);
-}
-
-constexpr int GEMM_KS = 128;               // k per LDS stage (four MFMA steps)
-constexpr int GEMM_KP = GEMM_KS + 8;       // padded LDS row, bf16
-
-// The 16-byte pieces of one stage of a 64-row operand tile X(r, k) (r = m of
-// A or n of B): piece e of thread tid.  kc: X is contiguous along k (pieces
-// run along k, 16 per row of the stage); else along r (8 per k-row).
-// Pieces outside 0 <= r < R or k < K are zero.
-DEV_EPI void tile_load(const uint16_t *X, long sr, long sk, bool kc, int r0, int R, int kb, int K, int tid,
-                       uint4 *out)
-{
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int c = e * 256 + tid;
-        const int r = kc ? c >> 4 : (c & 7) * 8, k = kc ? (c & 15) * 8 : c >> 3;
-        const int gr = r0 + r, gk = kb + k;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (gr < R && gk < K) v = *(const uint4 *)(X + (long)gr * sr + (long)gk * sk);
-        out[e] = v;
-    }
-}
-
-DEV_EPI void tile_store(uint16_t *L, bool kc, int tid, const uint4 *in)
-{
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int c = e * 256 + tid;
-        if (kc) {
-            *(uint4 *)&L[(c >> 4) * GEMM_KP + (c & 15) * 8] = in[e];
-        } else {                                  // eight rows, one k: transposed into LDS
-            const int r = (c & 7) * 8, k = c >> 3;
-            const uint32_t w[4] = {in[e].x, in[e].y, in[e].z, in[e].w};
-#pragma unroll
-            for (int i = 0; i < 8; ++i) L[(r + i) * GEMM_KP + k] = (uint16_t)(w[i >> 1] >> (16 * (i & 1)));
-        }
-    }
-}
-
-__global__ void __launch_bounds__(256) k_gemm(GemmArgs g)
-{
-    __shared__ __attribute__((aligned(16))) uint16_t As[2][64 * GEMM_KP];
-    __shared__ __attribute__((aligned(16))) uint16_t Bt[2][64 * GEMM_KP];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-    const int wm = (wave & 1) * 32, wn = (wave >> 1) * 32;
-    const int r = lane & 15, kq = (lane >> 4) * 8;
-    const int nstep = (g.K + 31) / 32;
-    const int s0 = (int)((long)nstep * blockIdx.z / gridDim.z), s1 = (int)((long)nstep * (blockIdx.z + 1) / gridDim.z);
-    // A as X(m, k): contiguous along k when sak == 1; B as X(n, k): along k when sbk == 1
-    const bool a_k = g.sak == 1, b_k = g.sbk == 1;
-    const long ar = g.sam, ak = g.sak, br = g.sbn, bk = g.sbk;
-    float4_t acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
-    const int kend = s1 * 32;
-    uint4 ra[4], rb[4];
-    int kb = s0 * 32;
-    if (kb < kend) {
-        tile_load(g.A, ar, ak, a_k, m0, g.M, kb, g.K, tid, ra);
-        tile_load(g.B, br, bk, b_k, n0, g.N, kb, g.K, tid, rb);
-    }
-    for (int buf = 0; kb < kend; kb += GEMM_KS, buf ^= 1) {
-        // the buffer written here was last read two stages ago, before the
-        // barrier of the previous stage
-        tile_store(As[buf], a_k, tid, ra);
-        tile_store(Bt[buf], b_k, tid, rb);
-        __syncthreads();
-        if (kb + GEMM_KS < kend) {
-            tile_load(g.A, ar, ak, a_k, m0, g.M, kb + GEMM_KS, g.K, tid, ra);
-            tile_load(g.B, br, bk, b_k, n0, g.N, kb + GEMM_KS, g.K, tid, rb);
-        }
-        const int nk = (kend - kb < GEMM_KS ? kend - kb : GEMM_KS) / 32;
-        for (int kk = 0; kk < nk; ++kk) {
-            bf16x8_t a[2], b[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) a[i] = *(const bf16x8_t *)&As[buf][(wm + 16 * i + r) * GEMM_KP + kk * 32 + kq];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) b[j] = *(const bf16x8_t *)&Bt[buf][(wn + 16 * j + r) * GEMM_KP + kk * 32 + kq];
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int m = m0 + wm + 16 * i + (lane >> 4) * 4 + t, n = n0 + wn + 16 * j + r;
-                if (m < g.M && n < g.N) {
-                    if (gridDim.z > 1) g.P[((long)blockIdx.z * g.M + m) * g.N + n] = acc[i][j][t];
-                    else gemm_store(g, m, n, acc[i][j][t]);
-                }
-            }
-}
-
-// C = the sum of the split-K partials in slice order, then bias / relu / stores
-__global__ void k_gemm_reduce(GemmArgs g, int nz)
-{
-    const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= (long)g.M * g.N) return;
-    float v = 0.f;
-    for (int z = 0; z < nz; ++z) v += g.P[(long)z * g.M * g.N + q];
-    gemm_store(g, (int)(q / g.N), (int)(q % g.N), v);
-}
-
-// logit, probability and (training) the weighted-BCE gradient per row:
-// z = sum_j H2[j] w3[j] + b3 (fp32, j ascending); dl/dz = (s (pw y + 1 - y) - pw y) / n
-__global__ void k_head(const uint16_t *H2, const uint16_t *w3, const float *b3, int n, const uint8_t *y,
-                       float pw, float *z, float *prob, float *dz, float *loss)
-{
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= n) return;
-    float s = 0.f;
-    for (int j = 0; j < IC_MLP_HID; ++j) s += bf2f(H2[(long)b * IC_MLP_HID + j]) * bf2f(w3[j]);
-    s += b3[0];
-    const float p = 1.f / (1.f + expf(-s));
-    if (z) z[b] = s;
-    if (prob) prob[b] = p;
-    if (y) {
-        const float yy = (float)y[b];
-        dz[b] = (p * (pw * yy + 1.f - yy) - pw * yy) / (float)n;
-        // stable log-sigmoid terms
-        const float lsp = s >= 0.f ? -log1pf(expf(-s)) : s - log1pf(expf(s));     // log p
-        const float lsn = s >= 0.f ? -s - log1pf(expf(-s)) : -log1pf(expf(s));   // log (1 - p)
-        loss[b] = -(pw * yy * lsp + (1.f - yy) * lsn);
-    }
-}
 
 // ---------------------------------------------------------------------------
 // inference in one launch: z-score, bf16 rounding of inputs and weights, both
@@ -293,28 +121,40 @@ DEV_EPI void weights_ask(const float *W, int wave, int lane, float (*v)[8])
         for (int e = 0; e < 8; ++e) v[kk][e] = q[(kk * 32 + e) * IC_MLP_HID];
 }
 
-// C rows 4 (l / 16) + 0..3, column l % 16 of a 16-row tile of L (rows of
-// `pitch` bf16) times the NK operands b
-template <int NK>
-DEV_EPI float4_t tile_mfma(const uint16_t *L, int pitch, int lane, const bf16x8_t *b)
+// C rows 16 i + 4 (l / 16) + 0..3, column l % 16, of the NB 16-row blocks of L
+// (rows of `pitch` bf16) times the NK operands b
+template <int NK, int NB>
+DEV_EPI void tile_mfma(const uint16_t *L, int pitch, int lane, const bf16x8_t *b, float4_t *acc)
 {
-    float4_t acc{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int kk = 0; kk < NK; ++kk) {
-        const bf16x8_t a = *(const bf16x8_t *)&L[(lane & 15) * pitch + kk * 32 + (lane >> 4) * 8];
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[kk], acc, 0, 0, 0);
-    }
-    return acc;
+    for (int i = 0; i < NB; ++i) acc[i] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk)
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const bf16x8_t a = *(const bf16x8_t *)&L[(16 * i + (lane & 15)) * pitch + kk * 32 + (lane >> 4) * 8];
+            acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[kk], acc[i], 0, 0, 0);
+            // no further than 16 operands read ahead: more would spill
+            if (NB > 1 && kk % 4 == 3 && i == NB - 1) __builtin_amdgcn_sched_barrier(0);
+        }
 }
 
 DEV_EPI float relu(float v) { return v > 0.f ? v : 0.f; }
 
-// logit of a row: sum_j H2[j] w3[j] + b3 (fp32, j ascending), w3 rounded to bf16
+// logit of a row: sum_j H2[j] w3[j] + b3 (fp32, j ascending), w3 rounded to
+// bf16; both 16-byte aligned in LDS
 DEV_EPI float head_row(const uint16_t *H2, const float *w3, float b3)
 {
     float s = 0.f;
-#pragma unroll 16
-    for (int j = 0; j < IC_MLP_HID; ++j) s += bf2f(H2[j]) * w3[j];
+#pragma unroll 4
+    for (int j = 0; j < IC_MLP_HID; j += 8) {
+        const uint4 h = *(const uint4 *)&H2[j];
+        const float4_t wa = *(const float4_t *)&w3[j], wb = *(const float4_t *)&w3[j + 4];
+        const uint32_t u[4] = {h.x, h.y, h.z, h.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            s += bf2f((uint16_t)(u[e >> 1] >> (16 * (e & 1)))) * (e < 4 ? wa[e & 3] : wb[e & 3]);
+    }
     return s + b3;
 }
 
@@ -374,11 +214,12 @@ k_infer(const void *x, const float *mean, const float *std, const float *P, int 
         }
         __syncthreads();
         if (tile + (int)gridDim.x < ntile) ask(tile + gridDim.x);
-        const float4_t z1 = tile_mfma<16>(Xs, NET_XP, lane, w1);
+        float4_t z1, z2;
+        tile_mfma<16, 1>(Xs, NET_XP, lane, w1, &z1);
 #pragma unroll
         for (int t = 0; t < 4; ++t) Hs[(row4 + t) * NET_HP + col] = f2bf(relu(z1[t] + b1));
         __syncthreads();
-        const float4_t z2 = tile_mfma<4>(Hs, NET_HP, lane, w2);
+        tile_mfma<4, 1>(Hs, NET_HP, lane, w2, &z2);
 #pragma unroll
         for (int t = 0; t < 4; ++t) Gs[(row4 + t) * NET_HP + col] = f2bf(relu(z2[t] + b2));
         __syncthreads();
@@ -390,80 +231,461 @@ k_infer(const void *x, const float *mean, const float *std, const float *P, int 
     }
 }
 
-// dZ2 = dz w3 [H2 > 0] (fp32 and bf16 copies)
-__global__ void k_back2(const float *dz, const uint16_t *w3, const uint16_t *H2, int n, float *dZ2, uint16_t *dZ2b)
-{
-    const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= (long)n * IC_MLP_HID) return;
-    const int b = (int)(q / IC_MLP_HID), j = (int)(q % IC_MLP_HID);
-    const float v = bf2f(H2[q]) > 0.f ? dz[b] * bf2f(w3[j]) : 0.f;
-    dZ2[q] = v;
-    dZ2b[q] = f2bf(v);
-}
+// ---------------------------------------------------------------------------
+// weight gradients: dW = A^T D over the n rows of a minibatch, bf16 operands,
+// fp32 accumulate on v_mfma_f32_16x16x32_bf16; dW1 (A = X, 512 columns) and
+// dW2 (A = H1, 128 columns) in one launch.  A work-group of 4 waves computes a
+// 64x64 tile of one slice of the rows, each wave a 32x32 quarter as 2x2 MFMA
+// blocks.  Rows advance in MFMA steps of 32, staged through LDS four steps at
+// a time and transposed there (row index contiguous), so that a lane's operand
+// -- one column and eight consecutive rows -- is one 16-byte LDS read (pitch
+// padded by 8 bf16 to spread them over the banks).  Each thread moves 16-byte
+// pieces (eight columns of a row); the next stage's loads are in flight while
+// the MFMAs of the current one run, from the other of two LDS buffers.  The
+// slices' fp32 sums go to P[slice][m][n]; k_update adds them in slice order.
+// 4,096 rows, both matrices: 17 us in two launches -> 7.4 us, of which pairs
+// of rows stored as one word and the order of tile_at gave 4.
+// ---------------------------------------------------------------------------
+struct GradArgs {
+    const uint16_t *A, *D;    // [n][M], [n][128]
+    int M, nz;                // columns of A, slices
+    float *P;                 // [nz][M][128]
+};
 
-// dZ1 = dH1 [H1 > 0]
-__global__ void k_mask(const float *dH, const uint16_t *H, long count, float *dZ, uint16_t *dZb)
-{
-    const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= count) return;
-    const float v = bf2f(H[q]) > 0.f ? dH[q] : 0.f;
-    dZ[q] = v;
-    dZb[q] = f2bf(v);
-}
+constexpr int GEMM_KS = 128;               // rows per LDS stage (four MFMA steps)
+constexpr int GEMM_KP = GEMM_KS + 8;       // padded LDS row, bf16
 
-// column sums out[j] = sum_b w[b] * M[b][j] (w = NULL: plain sums), fp32, in
-// two levels: chunk c of the rows (gridDim.y chunks, rows ascending within a
-// chunk) into P[c][j], then the chunks in order (k_colsum_reduce)
-__global__ void k_colsum(const float *Mf, const uint16_t *Mb, const float *w, int n, int ncol, float *P)
+// The pieces of one stage of a 64-column tile of X[n][ld], rows 2p and 2p + 1
+// of a piece in turn; rows from n on are zero.
+DEV_EPI void tile_load(const uint16_t *X, int ld, int c0, int kb, int n, int tid, uint4 *out)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= ncol) return;
-    const int c = blockIdx.y, nc = gridDim.y;
-    const int b0 = (int)((long)n * c / nc), b1 = (int)((long)n * (c + 1) / nc);
-    float s = 0.f;
-    for (int b = b0; b < b1; ++b) {
-        const float m = Mf ? Mf[(long)b * ncol + j] : bf2f(Mb[(long)b * ncol + j]);
-        s += w ? w[b] * m : m;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int k = kb + 2 * ((e >> 1) * 32 + (tid >> 3)) + (e & 1);
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (k < n) v = *(const uint4 *)(X + (long)k * ld + c0 + (tid & 7) * 8);
+        out[e] = v;
     }
-    P[(long)c * ncol + j] = s;
 }
 
-__global__ void k_colsum_reduce(const float *P, int nc, int ncol, float *out)
+// Column r's eight-row pieces lie in the order p ^ (r / 8 % 8): the eight
+// lanes that write one pair of rows then meet different banks (a row of 8
+// columns further is 32 banks on, whatever the padding).
+DEV_EPI int tile_at(int r, int k) { return r * GEMM_KP + (((k >> 3) ^ ((r >> 3) & 7)) << 3) + (k & 7); }
+
+DEV_EPI void tile_store(uint16_t *L, int tid, const uint4 *in)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= ncol) return;
-    float s = 0.f;
-    for (int c = 0; c < nc; ++c) s += P[(long)c * ncol + j];
-    out[j] = s;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int r = (tid & 7) * 8, k = 2 * (h * 32 + (tid >> 3));
+        const uint32_t a[4] = {in[2 * h].x, in[2 * h].y, in[2 * h].z, in[2 * h].w};
+        const uint32_t b[4] = {in[2 * h + 1].x, in[2 * h + 1].y, in[2 * h + 1].z, in[2 * h + 1].w};
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            *(uint32_t *)&L[tile_at(r + i, k)] =
+                __builtin_amdgcn_perm(b[i >> 1], a[i >> 1], i & 1 ? 0x07060302u : 0x05040100u);
+    }
 }
 
-// sum of the n per-row losses in fp64 (fixed order: thread-strided, then a
-// pairwise tree) into out[slot]
-__global__ void __launch_bounds__(256) k_loss_sum(const float *loss, int n, double *out, long slot)
+__global__ void __launch_bounds__(256) k_wgrad(GradArgs g1, GradArgs g2, int n)
 {
-    __shared__ double sh[256];
-    double s = 0.0;
-    for (int b = threadIdx.x; b < n; b += 256) s += (double)loss[b];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
+    __shared__ __attribute__((aligned(16))) uint16_t As[2][64 * GEMM_KP];
+    __shared__ __attribute__((aligned(16))) uint16_t Bt[2][64 * GEMM_KP];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    int q = blockIdx.x;
+    const int first = 2 * (g1.M / 64) * g1.nz;
+    const bool two = q >= first;
+    const GradArgs g = two ? g2 : g1;
+    if (two) q -= first;
+    const int n0 = (q & 1) * 64, m0 = ((q >> 1) % (g.M / 64)) * 64, z = (q >> 1) / (g.M / 64);
+    const int wm = (wave & 1) * 32, wn = (wave >> 1) * 32;
+    const int r = lane & 15, kq = (lane >> 4) * 8;
+    const int nstep = (n + 31) / 32;
+    const int s0 = (int)((long)nstep * z / g.nz), s1 = (int)((long)nstep * (z + 1) / g.nz);
+    float4_t acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
+    const int kend = s1 * 32;
+    uint4 ra[4], rb[4];
+    int kb = s0 * 32;
+    if (kb < kend) {
+        tile_load(g.A, g.M, m0, kb, n, tid, ra);
+        tile_load(g.D, IC_MLP_HID, n0, kb, n, tid, rb);
+    }
+    for (int buf = 0; kb < kend; kb += GEMM_KS, buf ^= 1) {
+        // the buffer written here was last read two stages ago, before the
+        // barrier of the previous stage
+        tile_store(As[buf], tid, ra);
+        tile_store(Bt[buf], tid, rb);
         __syncthreads();
+        if (kb + GEMM_KS < kend) {
+            tile_load(g.A, g.M, m0, kb + GEMM_KS, n, tid, ra);
+            tile_load(g.D, IC_MLP_HID, n0, kb + GEMM_KS, n, tid, rb);
+        }
+        const int nk = (kend - kb < GEMM_KS ? kend - kb : GEMM_KS) / 32;
+        for (int kk = 0; kk < nk; ++kk) {
+            bf16x8_t a[2], b[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) a[i] = *(const bf16x8_t *)&As[buf][tile_at(wm + 16 * i + r, kk * 32 + kq)];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) b[j] = *(const bf16x8_t *)&Bt[buf][tile_at(wn + 16 * j + r, kk * 32 + kq)];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
     }
-    if (threadIdx.x == 0) out[slot] = sh[0];
+    float *P = g.P + (long)z * g.M * IC_MLP_HID;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                P[(m0 + wm + 16 * i + (lane >> 4) * 4 + t) * IC_MLP_HID + n0 + wn + 16 * j + r] = acc[i][j][t];
 }
 
-__global__ void k_adam(float *w, uint16_t *wb, const float *g, float *m1, float *m2, int n, float lr, float b1,
-                       float b2, float eps, float c1, float c2)
+// ---------------------------------------------------------------------------
+// training: forward and backward of a minibatch's rows in one launch
+//
+// One work-group takes one chunk of the rows (the chunks in which the bias and
+// w3 gradients are summed), in tiles of 64: both layers, the head, the loss,
+// dZ2 = dz w3 [H2 > 0], dZ1 = (dZ2 W2^T) [H1 > 0] and the chunk's column sums
+// (rows ascending), with every operand between them in LDS.  What the weight
+// gradients need goes to memory as bf16: the gathered rows, H1, dZ2, dZ1.  The
+// weights come as packed operands (below), W2 a second time transposed.  Bound
+// by the latency of the phases of a tile (at 4,096 rows, where a chunk is one
+// tile: layers, dZ2 and dZ1 5 us, head 1.2, sums 0.7, the rest the rows and the
+// weights on their way; two tiles of 32 rows took 26 us).  A minibatch of 4,096 rows: 205 us in 17
+// launches -> 35 us in three, this one 21 us.
+// ---------------------------------------------------------------------------
+// The bf16 weights of k_rows, as each lane's 16-byte MFMA B operands: operand
+// (step kk, wave, lane) of W1, then W2, then W2^T.  k_update writes them with
+// the parameters, so that a work-group asks for 24 pieces a lane and rounds
+// nothing (192 fp32 values a lane and their rounding: 31 us a launch against 26).
+constexpr int PACK_W2 = IC_MLP_IN * IC_MLP_HID, PACK_W2T = PACK_W2 + IC_MLP_HID * IC_MLP_HID;
+constexpr int PACK_N = PACK_W2T + IC_MLP_HID * IC_MLP_HID;
+
+DEV_EPI int pack_at(int k, int n)
+{
+    return ((((k >> 5) * 8 + (n >> 4)) * 64) + ((k >> 3) & 3) * 16 + (n & 15)) * 8 + (k & 7);
+}
+
+// parameter q as bf16 to its places (biases and w3 have none)
+DEV_EPI void pack_param(uint16_t *wp, int q, float w)
+{
+    if (q < IC_MLP_OFF_B1) {
+        wp[pack_at(q / IC_MLP_HID, q % IC_MLP_HID)] = f2bf(w);
+    } else if (q >= IC_MLP_OFF_W2 && q < IC_MLP_OFF_B2) {
+        const int k = (q - IC_MLP_OFF_W2) / IC_MLP_HID, n = (q - IC_MLP_OFF_W2) % IC_MLP_HID;
+        const uint16_t b = f2bf(w);
+        wp[PACK_W2 + pack_at(k, n)] = b;
+        wp[PACK_W2T + pack_at(n, k)] = b;
+    }
+}
+
+__global__ void k_pack(const float *w, uint16_t *wp)
 {
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n) return;
-    const float gg = g[q];
-    m1[q] = b1 * m1[q] + (1.f - b1) * gg;
-    m2[q] = b2 * m2[q] + (1.f - b2) * gg * gg;
-    const float mh = m1[q] / c1, vh = m2[q] / c2;
-    w[q] -= lr * mh / (sqrtf(vh) + eps);
-    if (wb) wb[q] = f2bf(w[q]);
+    if (q < IC_MLP_NPARAM) pack_param(wp, q, w[q]);
+}
+
+constexpr int ROWS_T = 64, ROWS_NB = ROWS_T / 16;   // rows of a tile, MFMA blocks
+constexpr int ROWS_FP = IC_MLP_HID + 4;             // padded fp32 row of dZ1
+constexpr int SUMS = 3 * IC_MLP_HID + 1;            // column sums of a chunk: db1, db2, dw3, db3
+
+struct RowArgs {
+    const uint16_t *X;        // normalised inputs, bf16
+    const long *order;        // GATHER: row b of the minibatch is order[b] of X and y; else row b
+    const uint8_t *y;
+    const float *P;           // parameters
+    const uint16_t *wp;       // their packed bf16 weights
+    int n;                    // rows
+    float pw;
+    uint16_t *xb;             // GATHER: the gathered rows
+    uint16_t *H1, *dZ2, *dZ1;
+    float *loss;              // per row
+    float *S;                 // [chunks][SUMS]
+};
+
+template <bool GATHER>
+__global__ void __launch_bounds__(NET_TH) __attribute__((amdgpu_waves_per_eu(2, 2))) k_rows(RowArgs g)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t Xs[ROWS_T * NET_XP];
+    __shared__ __attribute__((aligned(16))) uint16_t Hs[ROWS_T * NET_HP], Gs[ROWS_T * NET_HP], Ds[ROWS_T * NET_HP];
+    __shared__ __attribute__((aligned(16))) float Fs[ROWS_T * ROWS_FP];
+    __shared__ __attribute__((aligned(16))) float w3s[IC_MLP_HID], dzs[ROWS_T];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int col = wave * 16 + (lane & 15), row4 = (lane >> 4) * 4;
+    const int b0 = (int)((long)g.n * blockIdx.x / gridDim.x), b1 = (int)((long)g.n * (blockIdx.x + 1) / gridDim.x);
+    // A tile's rows, one a lane (from b1 on the last one again: read, not
+    // used), asked for a tile ahead of the inputs: wave w moves rows w, w + 8,
+    // ..., a 16-byte piece a lane.
+    constexpr int NX = ROWS_T / 8;
+    long idx;
+    u32x4_t xr[NX];
+    uint8_t yr = 0;
+    auto ask_rows = [&](int t0) {
+        const int b = min(t0 + lane, b1 - 1);
+        idx = GATHER ? g.order[b] : (long)b;
+    };
+    auto ask = [&]() {
+        const int lo = (int)idx, hi = (int)(idx >> 32), w = __builtin_amdgcn_readfirstlane(wave);
+#pragma unroll
+        for (int e = 0; e < NX; ++e) {
+            const long row = (long)(uint32_t)__builtin_amdgcn_readlane(lo, e * 8 + w) |
+                             (long)__builtin_amdgcn_readlane(hi, e * 8 + w) << 32;
+            xr[e] = ((const u32x4_t *)g.X)[row * (IC_MLP_IN / 8) + lane];
+        }
+        if (wave == 0) yr = g.y[idx];
+    };
+    ask_rows(b0);
+    bf16x8_t w1[16], w2[4], w2t[4];
+    const bf16x8_t *wp = (const bf16x8_t *)g.wp + wave * 64 + lane;
+#pragma unroll
+    for (int kk = 0; kk < 16; ++kk) w1[kk] = wp[kk * 512];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+        w2[kk] = wp[PACK_W2 / 8 + kk * 512];
+        w2t[kk] = wp[PACK_W2T / 8 + kk * 512];
+    }
+    const float bias1 = g.P[IC_MLP_OFF_B1 + col], bias2 = g.P[IC_MLP_OFF_B2 + col], bias3 = g.P[IC_MLP_OFF_B3];
+    if (tid < IC_MLP_HID) w3s[tid] = bf2f(f2bf(g.P[IC_MLP_OFF_W3 + tid]));
+    ask();
+    ask_rows(b0 + ROWS_T);
+    float sum = 0.f;                        // this thread's column sum over the chunk
+    for (int t0 = b0; t0 < b1; t0 += ROWS_T) {
+        const int nr = min(ROWS_T, b1 - t0);
+#pragma unroll
+        for (int e = 0; e < NX; ++e) *(u32x4_t *)&Xs[(e * 8 + wave) * NET_XP + lane * 8] = xr[e];
+        if (GATHER) {                        // rows past the chunk write its last row once more
+#pragma unroll
+            for (int e = 0; e < NX; ++e)
+                ((u32x4_t *)g.xb)[(long)min(t0 + e * 8 + wave, b1 - 1) * (IC_MLP_IN / 8) + lane] = xr[e];
+        }
+        const float yy = (float)yr;
+        __syncthreads();
+        if (t0 + ROWS_T < b1) {
+            ask();
+            ask_rows(t0 + 2 * ROWS_T);
+        }
+        float4_t z[ROWS_NB];
+        tile_mfma<16, ROWS_NB>(Xs, NET_XP, lane, w1, z);
+#pragma unroll
+        for (int q = 0; q < 4 * ROWS_NB; ++q)
+            Hs[(16 * (q >> 2) + row4 + (q & 3)) * NET_HP + col] = f2bf(relu(z[q >> 2][q & 3] + bias1));
+        __syncthreads();
+        tile_mfma<4, ROWS_NB>(Hs, NET_HP, lane, w2, z);
+#pragma unroll
+        for (int q = 0; q < 4 * ROWS_NB; ++q)
+            Gs[(16 * (q >> 2) + row4 + (q & 3)) * NET_HP + col] = f2bf(relu(z[q >> 2][q & 3] + bias2));
+        __syncthreads();
+        if (tid < ROWS_T) {
+            float dz = 0.f;
+            if (tid < nr) {
+                const float s = head_row(&Gs[tid * NET_HP], w3s, bias3);
+                const float p = 1.f / (1.f + expf(-s)), pw = g.pw;
+                const int b = t0 + tid;
+                // gradient of the mean weighted BCE
+                dz = (p * (pw * yy + 1.f - yy) - pw * yy) / (float)g.n;
+                // stable log-sigmoid terms: log p and log (1 - p)
+                const float l = log1pf(expf(s >= 0.f ? -s : s));
+                const float lsp = s >= 0.f ? -l : s - l;
+                const float lsn = s >= 0.f ? -s - l : -l;
+                g.loss[b] = -(pw * yy * lsp + (1.f - yy) * lsn);
+            }
+            dzs[tid] = dz;
+        }
+        __syncthreads();
+        // this thread's eights of the 64 x 128 arrays: columns ec.., rows er and er + 32
+        const int er = tid >> 4, ec = (tid & 15) * 8;
+#pragma unroll
+        for (int r = er; r < ROWS_T; r += NET_TH / 16) {
+            float v[8];
+            const float dz = dzs[r];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = bf2f(Gs[r * NET_HP + ec + e]) > 0.f ? dz * w3s[ec + e] : 0.f;
+            const bf16x8_t d = pack8(v);
+            *(bf16x8_t *)&Ds[r * NET_HP + ec] = d;
+            if (r < nr) {
+                *(bf16x8_t *)&g.dZ2[(long)(t0 + r) * IC_MLP_HID + ec] = d;
+                *(uint4 *)&g.H1[(long)(t0 + r) * IC_MLP_HID + ec] = *(const uint4 *)&Hs[r * NET_HP + ec];
+            }
+        }
+        __syncthreads();
+        tile_mfma<4, ROWS_NB>(Ds, NET_HP, lane, w2t, z);
+#pragma unroll
+        for (int q = 0; q < 4 * ROWS_NB; ++q) {
+            const int r = 16 * (q >> 2) + row4 + (q & 3);
+            Fs[r * ROWS_FP + col] = bf2f(Hs[r * NET_HP + col]) > 0.f ? z[q >> 2][q & 3] : 0.f;
+        }
+        __syncthreads();
+        // column sums, rows ascending, sixteen LDS reads in flight; waves 0-1
+        // db1, 2-3 db2, 4-5 dw3, then db3
+        const int j = tid & (IC_MLP_HID - 1);
+        auto add_rows = [&](auto term) {
+            int r = 0;
+#pragma unroll 1
+            for (; r + 16 <= nr; r += 16) {
+                float v[16];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) v[e] = term(r + e);
+#pragma unroll
+                for (int e = 0; e < 16; ++e) sum += v[e];
+            }
+#pragma unroll 1
+            for (; r < nr; ++r) sum += term(r);
+        };
+        if (wave < 2) add_rows([&](int r) { return Fs[r * ROWS_FP + j]; });
+        else if (wave < 4) add_rows([&](int r) { return bf2f(Gs[r * NET_HP + j]) > 0.f ? dzs[r] * w3s[j] : 0.f; });
+        else if (wave < 6) add_rows([&](int r) { return dzs[r] * bf2f(Gs[r * NET_HP + j]); });
+        else if (wave < 7) add_rows([&](int r) { return dzs[r]; });
+#pragma unroll
+        for (int r = er; r < ROWS_T; r += NET_TH / 16)
+            if (r < nr) *(bf16x8_t *)&g.dZ1[(long)(t0 + r) * IC_MLP_HID + ec] = pack8(&Fs[r * ROWS_FP + ec]);
+        // the next tile's first barriers order these reads before its writes
+    }
+    if (tid < SUMS) g.S[(long)blockIdx.x * SUMS + tid] = sum;
+}
+
+// The minibatch's gradient from its partial sums -- slices of the weights'
+// (k_wgrad) and chunks of the others' (k_rows), each in order -- and Adam's
+// step with it, or (grad) the gradient itself.  The group after the
+// parameters' sums the rows' losses in fp64 (fixed order: thread-strided, then
+// a pairwise tree).
+struct StepArgs {
+    const float *P1, *P2, *S;
+    int nz1, nz2, nc;
+    float *grad;                           // the gradient; NULL: Adam
+    float *w, *m1, *m2;
+    uint16_t *wp;                          // packed weights
+    float lr, b1, b2, eps, c1, c2;
+    const float *loss;
+    int n;
+    double *loss_out;
+};
+
+DEV_EPI float ordered_sum(const float *p, int count, int stride)
+{
+    float s = 0.f;
+    int z = 0;
+    for (; z + 16 <= count; z += 16) {
+        float v[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = p[(z + e) * stride];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s += v[e];
+    }
+    for (; z < count; ++z) s += p[z * stride];
+    return s;
+}
+
+__global__ void __launch_bounds__(256) k_update(StepArgs g)
+{
+    const int q = blockIdx.x * 256 + threadIdx.x;
+    if (blockIdx.x == gridDim.x - 1) {
+        __shared__ double sh[256];
+        double s = 0.0;
+        for (int b = threadIdx.x; b < g.n; b += 256) s += (double)g.loss[b];
+        sh[threadIdx.x] = s;
+        __syncthreads();
+        for (int w = 128; w > 0; w >>= 1) {
+            if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) *g.loss_out = sh[0];
+        return;
+    }
+    if (q >= IC_MLP_NPARAM) return;
+    float gg;
+    if (q < IC_MLP_OFF_B1) gg = ordered_sum(g.P1 + q, g.nz1, IC_MLP_IN * IC_MLP_HID);
+    else if (q < IC_MLP_OFF_W2) gg = ordered_sum(g.S + (q - IC_MLP_OFF_B1), g.nc, SUMS);
+    else if (q < IC_MLP_OFF_B2) gg = ordered_sum(g.P2 + (q - IC_MLP_OFF_W2), g.nz2, IC_MLP_HID * IC_MLP_HID);
+    else gg = ordered_sum(g.S + IC_MLP_HID + (q - IC_MLP_OFF_B2), g.nc, SUMS);      // db2, dw3, db3
+    if (g.grad) {
+        g.grad[q] = gg;
+        return;
+    }
+    const float m1 = g.b1 * g.m1[q] + (1.f - g.b1) * gg;
+    const float m2 = g.b2 * g.m2[q] + (1.f - g.b2) * gg * gg;
+    g.m1[q] = m1;
+    g.m2[q] = m2;
+    const float mh = m1 / g.c1, vh = m2 / g.c2;
+    float w = g.w[q];
+    w -= g.lr * mh / (sqrtf(vh) + g.eps);
+    g.w[q] = w;
+    pack_param(g.wp, q, w);
+}
+
+// z-score statistics of n rows x 512 columns in fp64, rows ascending within a
+// column: mu (MEAN) or the sum of (x - mu)^2.  A column's sum is one chain of
+// n dependent additions, so a work-group takes 16 columns: all 16 waves bring
+// tiles of 512 rows (64 bytes a row) into LDS as the terms of the sum, and 16
+// lanes of the first wave add the previous tile meanwhile: 0.27 ms a pass over
+// 40,000 rows, 16 cycles an addition (on the host, and after the upload, both
+// passes took about 9 ms).
+constexpr int STAT_C = 16, STAT_R = 512, STAT_P = STAT_C + 1;
+
+template <bool MEAN>
+__global__ void __launch_bounds__(1024) k_stats(const float *raw, long n, double *mu, double *var)
+{
+    __shared__ double T[2][STAT_R * STAT_P];
+    const int tid = threadIdx.x, f0 = blockIdx.x * STAT_C;
+    const int c4 = (tid & 3) * 4, r = tid >> 2;                  // four columns of rows r and r + 256
+    double m[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m[e] = MEAN ? 0.0 : mu[f0 + c4 + e];
+    float4 v[2];
+    auto ask = [&](long b) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            v[h] = b + r + 256 * h < n ? *(const float4 *)(raw + (b + r + 256 * h) * IC_MLP_IN + f0 + c4)
+                                       : make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    double sum = 0.0;
+    ask(0);
+    int buf = 0;
+    for (long b = 0; b < n; b += STAT_R, buf ^= 1) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float x[4] = {v[h].x, v[h].y, v[h].z, v[h].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                double d = (double)x[e];
+                if (!MEAN) {
+                    d = d - m[e];
+                    d = d * d;
+                }
+                T[buf][(r + 256 * h) * STAT_P + c4 + e] = d;
+            }
+        }
+        __syncthreads();               // the other buffer was read before this barrier
+        if (b + STAT_R < n) ask(b + STAT_R);
+        if (tid < STAT_C) {
+            const int nr = (int)min((long)STAT_R, n - b);
+            const double *q = &T[buf][tid];
+            int i = 0;
+            double d[2][16];           // the next sixteen terms are read while these are added
+            auto get = [&](int i0, double *t) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) t[e] = q[(i0 + e) * STAT_P];
+            };
+            get(0, d[0]);
+            for (; i + 32 <= nr; i += 32) {
+                get(i + 16, d[1]);
+#pragma unroll
+                for (int e = 0; e < 16; ++e) sum += d[0][e];
+                get(min(i + 32, STAT_R - 16), d[0]);
+#pragma unroll
+                for (int e = 0; e < 16; ++e) sum += d[1][e];
+            }
+            for (; i < nr; ++i) sum += q[i * STAT_P];
+        }
+    }
+    if (tid < STAT_C) (MEAN ? mu : var)[f0 + tid] = MEAN ? sum / (double)n : sum;
 }
 
 __global__ void k_to_bf16(const float *x, uint16_t *y, long n)
@@ -481,18 +703,6 @@ __global__ void k_normalise(const float *raw, const float *mean, const float *is
     xb[q] = f2bf((raw[q] - mean[f]) * istd[f]);
 }
 
-// minibatch gather: rows order[b0 + q] of the normalised inputs and labels
-__global__ void k_gather(const uint16_t *xall, const uint8_t *yall, const long *order, long b0, int B, uint16_t *xb,
-                         uint8_t *yb)
-{
-    const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= (long)B * IC_MLP_IN) return;
-    const int r = (int)(q / IC_MLP_IN), f = (int)(q % IC_MLP_IN);
-    const long row = order[b0 + r];
-    xb[q] = xall[row * IC_MLP_IN + f];
-    if (f == 0) yb[r] = yall[row];
-}
-
 // learned flags: p >= threshold -> refine, else coarsen-eligible
 __global__ void k_prob_flags(const float *prob, const int *items, int n, float threshold, int8_t *flags)
 {
@@ -504,42 +714,6 @@ __global__ void k_prob_flags(const float *prob, const int *items, int n, float t
 // host side
 // ---------------------------------------------------------------------------
 namespace {
-
-// Split K only when a workspace is given (the weight gradients): enough
-// slices for ~256 work-groups, each at least 4 k-steps; the workspace holds
-// GEMM_SPLIT_MAX x M x N floats.
-constexpr int GEMM_SPLIT_MAX = 32;
-
-void gemm(hipStream_t s, const uint16_t *A, long sam, long sak, const uint16_t *B, long sbk, long sbn, int M, int N,
-          int K, const float *bias, int relu, float *Cf, uint16_t *Cb, long ldc, float *work = nullptr)
-{
-    // the stage loads move 16-byte pieces along the contiguous index of each
-    // operand: a unit stride, the other stride and that index's extent
-    // multiples of 8, 16-byte aligned bases (every call of this file)
-    const bool a_ok = (sak == 1 && sam % 8 == 0 && K % 8 == 0) || (sam == 1 && sak % 8 == 0 && M % 8 == 0);
-    const bool b_ok = (sbk == 1 && sbn % 8 == 0 && K % 8 == 0) || (sbn == 1 && sbk % 8 == 0 && N % 8 == 0);
-    if (!a_ok || !b_ok || ((uintptr_t)A & 15) || ((uintptr_t)B & 15))
-        throw std::runtime_error("gemm: operand layout not supported by the staged loads");
-    GemmArgs g{A, sam, sak, B, sbk, sbn, M, N, K, bias, relu, Cf, Cb, ldc, work};
-    const int tiles = ((N + 63) / 64) * ((M + 63) / 64), nstep = (K + 31) / 32;
-    int nz = 1;
-    if (work && tiles < 256) nz = std::max(1, std::min({GEMM_SPLIT_MAX, nstep / 4, (256 + tiles - 1) / tiles}));
-    dim3 grid((N + 63) / 64, (M + 63) / 64, nz);
-    hipLaunchKernelGGL(k_gemm, grid, dim3(256), 0, s, g);
-    if (nz > 1)
-        hipLaunchKernelGGL(k_gemm_reduce, dim3(((long)M * N + 255) / 256), dim3(256), 0, s, g, nz);
-}
-
-// column sums through the workspace (COLSUM_CHUNKS x ncol floats)
-constexpr int COLSUM_CHUNKS = 64;
-
-void colsum(hipStream_t s, const float *Mf, const uint16_t *Mb, const float *w, int n, int ncol, float *out,
-            float *work)
-{
-    const int nc = std::max(1, std::min(COLSUM_CHUNKS, n / 32));
-    hipLaunchKernelGGL(k_colsum, dim3((ncol + 127) / 128, nc), dim3(128), 0, s, Mf, Mb, w, n, ncol, work);
-    hipLaunchKernelGGL(k_colsum_reduce, dim3((ncol + 127) / 128), dim3(128), 0, s, (const float *)work, nc, ncol, out);
-}
 
 template <class T>
 struct Buf {
@@ -628,64 +802,74 @@ void mlp_prob_flags(hipStream_t s, const float *prob, const int *items, int n, f
     hipLaunchKernelGGL(k_prob_flags, dim3((n + 255) / 256), dim3(256), 0, s, prob, items, n, threshold, flags);
 }
 
-// One forward + backward pass on n rows: gradients (fp32, params layout) and mean loss.
-// X: normalised fp32 inputs (converted to bf16 here), params: fp32 master weights.
-// Workspace of fwd_bwd: split-K partials of the largest weight gradient, or
-// the chunked column sums
-constexpr size_t FWD_BWD_WORK = (size_t)GEMM_SPLIT_MAX * IC_MLP_IN * IC_MLP_HID;
+// The buffers and launches of one forward and backward pass of n rows.
+struct Pass {
+    int n, nc, nz1, nz2;
+    Buf<uint16_t> wp, H1, dZ2, dZ1;
+    Buf<float> loss, P1, P2, S;
+    // Slices of the rows in the weight gradients: enough for about 256
+    // work-groups a matrix, at most 32, each at least 4 MFMA steps.
+    static int slices(int n, int tiles) { return std::max(1, std::min({32, (n + 31) / 32 / 4, (256 + tiles - 1) / tiles})); }
+    explicit Pass(int n_)
+        : n(n_), nc(std::max(1, std::min(64, n_ / 32))), nz1(slices(n_, 2 * IC_MLP_IN / 64)),
+          nz2(slices(n_, 2 * IC_MLP_HID / 64)), wp(PACK_N), H1((size_t)n_ * IC_MLP_HID), dZ2((size_t)n_ * IC_MLP_HID),
+          dZ1((size_t)n_ * IC_MLP_HID), loss(n_), P1((size_t)nz1 * IC_MLP_IN * IC_MLP_HID),
+          P2((size_t)nz2 * IC_MLP_HID * IC_MLP_HID), S((size_t)nc * SUMS)
+    {
+    }
+    // the packed weights of the first pass; each Adam step then leaves the next one's
+    void pack(hipStream_t s, const float *w)
+    {
+        hipLaunchKernelGGL(k_pack, dim3((IC_MLP_NPARAM + 255) / 256), dim3(256), 0, s, w, wp.p);
+    }
+    // X, y: all rows; order: the minibatch's (NULL: rows 0 .. n-1); xb: room for its gathered inputs
+    void run(hipStream_t s, const uint16_t *X, const long *order, const uint8_t *y, float pw, const float *w,
+             uint16_t *xb, StepArgs st)
+    {
+        RowArgs r{X, order, y, w, wp.p, n, pw, xb, H1.p, dZ2.p, dZ1.p, loss.p, S.p};
+        if (order) hipLaunchKernelGGL((k_rows<true>), dim3(nc), dim3(NET_TH), 0, s, r);
+        else hipLaunchKernelGGL((k_rows<false>), dim3(nc), dim3(NET_TH), 0, s, r);
+        GradArgs g1{order ? xb : X, dZ1.p, IC_MLP_IN, nz1, P1.p}, g2{H1.p, dZ2.p, IC_MLP_HID, nz2, P2.p};
+        hipLaunchKernelGGL(k_wgrad, dim3(2 * (IC_MLP_IN / 64) * nz1 + 2 * (IC_MLP_HID / 64) * nz2), dim3(256), 0, s,
+                           g1, g2, n);
+        st.wp = wp.p;
+        st.P1 = P1.p;
+        st.P2 = P2.p;
+        st.S = S.p;
+        st.nz1 = nz1;
+        st.nz2 = nz2;
+        st.nc = nc;
+        st.loss = loss.p;
+        st.n = n;
+        hipLaunchKernelGGL(k_update, dim3((IC_MLP_NPARAM + 255) / 256 + 1), dim3(256), 0, s, st);
+    }
+};
 
-static void fwd_bwd(hipStream_t s, int n, const uint16_t *Xb, const uint8_t *y, float pw, const float *w,
-                    const uint16_t *wb, float *grad, float *loss_rows, Buf<uint16_t> &H1, Buf<uint16_t> &H2,
-                    Buf<float> &dz, Buf<float> &dZ2, Buf<uint16_t> &dZ2b, Buf<float> &dH1, Buf<float> &dZ1,
-                    Buf<uint16_t> &dZ1b, float *work)
-{
-    const uint16_t *W1 = wb + IC_MLP_OFF_W1, *W2 = wb + IC_MLP_OFF_W2, *w3 = wb + IC_MLP_OFF_W3;
-    gemm(s, Xb, IC_MLP_IN, 1, W1, IC_MLP_HID, 1, n, IC_MLP_HID, IC_MLP_IN, w + IC_MLP_OFF_B1, 1, nullptr, H1.p,
-         IC_MLP_HID);
-    gemm(s, H1.p, IC_MLP_HID, 1, W2, IC_MLP_HID, 1, n, IC_MLP_HID, IC_MLP_HID, w + IC_MLP_OFF_B2, 1, nullptr,
-         H2.p, IC_MLP_HID);
-    hipLaunchKernelGGL(k_head, dim3((n + 255) / 256), dim3(256), 0, s, H2.p, w3, w + IC_MLP_OFF_B3, n, y, pw,
-                       (float *)nullptr, (float *)nullptr, dz.p, loss_rows);
-    // layer 3: dw3 = H2^T dz, db3 = sum dz
-    colsum(s, nullptr, H2.p, dz.p, n, IC_MLP_HID, grad + IC_MLP_OFF_W3, work);
-    colsum(s, dz.p, nullptr, nullptr, n, 1, grad + IC_MLP_OFF_B3, work);
-    const long nh = (long)n * IC_MLP_HID;
-    hipLaunchKernelGGL(k_back2, dim3((nh + 255) / 256), dim3(256), 0, s, dz.p, w3, H2.p, n, dZ2.p, dZ2b.p);
-    colsum(s, dZ2.p, nullptr, nullptr, n, IC_MLP_HID, grad + IC_MLP_OFF_B2, work);
-    // dW2 = H1^T dZ2   (M = 128 (k of layer 2), N = 128, K = n)
-    gemm(s, H1.p, 1, IC_MLP_HID, dZ2b.p, IC_MLP_HID, 1, IC_MLP_HID, IC_MLP_HID, n, nullptr, 0, grad + IC_MLP_OFF_W2,
-         nullptr, IC_MLP_HID, work);
-    // dH1 = dZ2 W2^T   (B(k, j) = W2[j][k])
-    gemm(s, dZ2b.p, IC_MLP_HID, 1, W2, 1, IC_MLP_HID, n, IC_MLP_HID, IC_MLP_HID, nullptr, 0, dH1.p, nullptr,
-         IC_MLP_HID);
-    hipLaunchKernelGGL(k_mask, dim3((nh + 255) / 256), dim3(256), 0, s, dH1.p, H1.p, nh, dZ1.p, dZ1b.p);
-    colsum(s, dZ1.p, nullptr, nullptr, n, IC_MLP_HID, grad + IC_MLP_OFF_B1, work);
-    // dW1 = X^T dZ1    (M = 512, N = 128, K = n)
-    gemm(s, Xb, 1, IC_MLP_IN, dZ1b.p, IC_MLP_HID, 1, IC_MLP_IN, IC_MLP_HID, n, nullptr, 0, grad + IC_MLP_OFF_W1,
-         nullptr, IC_MLP_HID, work);
-}
-
+// Gradients (fp32, params layout) and mean loss of n rows of normalised fp32
+// inputs (converted to bf16 here); params: fp32 weights.
 void mlp_grad(const float *xnorm, const uint8_t *y, int n, float pw, const float *params, float *grad_out,
               float *loss_out)
 {
     hipStream_t s = nullptr;
-    Buf<float> x((size_t)n * IC_MLP_IN), w(IC_MLP_NPARAM), grad(IC_MLP_NPARAM), dz(n), loss(n), dZ2((size_t)n * IC_MLP_HID),
-        dH1((size_t)n * IC_MLP_HID), dZ1((size_t)n * IC_MLP_HID);
-    Buf<uint16_t> xb((size_t)n * IC_MLP_IN), wb(IC_MLP_NPARAM), H1((size_t)n * IC_MLP_HID), H2((size_t)n * IC_MLP_HID),
-        dZ2b((size_t)n * IC_MLP_HID), dZ1b((size_t)n * IC_MLP_HID);
+    Buf<float> x((size_t)n * IC_MLP_IN), w(IC_MLP_NPARAM), grad(IC_MLP_NPARAM);
+    Buf<uint16_t> xb((size_t)n * IC_MLP_IN);
     Buf<uint8_t> yd(n);
-    Buf<float> work(FWD_BWD_WORK);
+    Buf<double> lsum(1);
+    Pass pass(n);
     if (hipMemcpy(x.p, xnorm, (size_t)n * IC_MLP_IN * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(w.p, params, IC_MLP_NPARAM * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(yd.p, y, n, hipMemcpyHostToDevice) != hipSuccess)
         throw std::runtime_error("hipMemcpy failed");
     hipLaunchKernelGGL(k_to_bf16, dim3(((long)n * IC_MLP_IN + 255) / 256), dim3(256), 0, s, x.p, xb.p,
                        (long)n * IC_MLP_IN);
-    hipLaunchKernelGGL(k_to_bf16, dim3((IC_MLP_NPARAM + 255) / 256), dim3(256), 0, s, w.p, wb.p, (long)IC_MLP_NPARAM);
-    fwd_bwd(s, n, xb.p, yd.p, pw, w.p, wb.p, grad.p, loss.p, H1, H2, dz, dZ2, dZ2b, dH1, dZ1, dZ1b, work.p);
+    pass.pack(s, w.p);
+    StepArgs st{};
+    st.grad = grad.p;
+    st.loss_out = lsum.p;
+    pass.run(s, xb.p, nullptr, yd.p, pw, w.p, nullptr, st);
     std::vector<float> lrow(n);
     if (hipMemcpy(grad_out, grad.p, IC_MLP_NPARAM * sizeof(float), hipMemcpyDeviceToHost) != hipSuccess ||
-        hipMemcpy(lrow.data(), loss.p, n * sizeof(float), hipMemcpyDeviceToHost) != hipSuccess)
+        hipMemcpy(lrow.data(), pass.loss.p, n * sizeof(float), hipMemcpyDeviceToHost) != hipSuccess)
         throw std::runtime_error("hipMemcpy failed");
     double l = 0.0;
     for (int b = 0; b < n; ++b) l += lrow[b];
@@ -696,52 +880,32 @@ void mlp_train(const float *raw, const uint8_t *y, long n, const MlpHparams &hp,
                float *std_out, float *loss_epochs)
 {
     hipStream_t s = nullptr;
-    // per-feature z-score statistics of the training set (fp64 on the host)
-    std::vector<double> mu(IC_MLP_IN, 0.0), var(IC_MLP_IN, 0.0);
-    for (long b = 0; b < n; ++b)
-        for (int f = 0; f < IC_MLP_IN; ++f) mu[f] += raw[b * IC_MLP_IN + f];
-    for (int f = 0; f < IC_MLP_IN; ++f) mu[f] /= (double)n;
-    for (long b = 0; b < n; ++b)
-        for (int f = 0; f < IC_MLP_IN; ++f) {
-            const double d = raw[b * IC_MLP_IN + f] - mu[f];
-            var[f] += d * d;
-        }
-    std::vector<float> mean_h(IC_MLP_IN), std_h(IC_MLP_IN), istd_h(IC_MLP_IN);
-    for (int f = 0; f < IC_MLP_IN; ++f) {
-        mean_h[f] = (float)mu[f];
-        double sd = std::sqrt(var[f] / (double)n);
-        if (!(sd > 1e-6)) sd = 1.0;
-        std_h[f] = (float)sd;
-        istd_h[f] = 1.0f / std_h[f];
-    }
-    long npos = 0;
-    for (long b = 0; b < n; ++b) npos += y[b] ? 1 : 0;
-    const float pw = hp.pos_weight > 0.f ? hp.pos_weight : (npos > 0 ? (float)(n - npos) / (float)npos : 1.f);
-    const int B = hp.batch;
-    Buf<float> rawd((size_t)n * IC_MLP_IN), mean(IC_MLP_IN), istd(IC_MLP_IN), w(IC_MLP_NPARAM), grad(IC_MLP_NPARAM),
-        m1(IC_MLP_NPARAM), m2(IC_MLP_NPARAM), dz(B), loss(B), dZ2((size_t)B * IC_MLP_HID), dH1((size_t)B * IC_MLP_HID),
-        dZ1((size_t)B * IC_MLP_HID);
-    Buf<uint16_t> xall((size_t)n * IC_MLP_IN), xb((size_t)B * IC_MLP_IN), wb(IC_MLP_NPARAM), H1((size_t)B * IC_MLP_HID),
-        H2((size_t)B * IC_MLP_HID), dZ2b((size_t)B * IC_MLP_HID), dZ1b((size_t)B * IC_MLP_HID);
-    Buf<uint8_t> yall(n), yb(B);
-    Buf<long> orderd(n);
-    Buf<float> work(FWD_BWD_WORK);
-    const long nbatch = n / B;
-    Buf<double> lossacc(std::max(nbatch, 1L));           // per-minibatch loss sums, read once per epoch
     auto H2D = [](void *d, const void *h, size_t bytes) {
         if (hipMemcpy(d, h, bytes, hipMemcpyHostToDevice) != hipSuccess) throw std::runtime_error("hipMemcpy failed");
     };
+    auto D2H = [](void *h, const void *d, size_t bytes) {
+        if (hipMemcpy(h, d, bytes, hipMemcpyDeviceToHost) != hipSuccess) throw std::runtime_error("hipMemcpy failed");
+    };
+    Buf<float> rawd((size_t)n * IC_MLP_IN), mean(IC_MLP_IN), istd(IC_MLP_IN), w(IC_MLP_NPARAM), m1(IC_MLP_NPARAM),
+        m2(IC_MLP_NPARAM);
+    Buf<double> stat(2 * IC_MLP_IN);
     H2D(rawd.p, raw, (size_t)n * IC_MLP_IN * sizeof(float));
-    H2D(mean.p, mean_h.data(), IC_MLP_IN * sizeof(float));
-    H2D(istd.p, istd_h.data(), IC_MLP_IN * sizeof(float));
-    H2D(w.p, params, IC_MLP_NPARAM * sizeof(float));
-    H2D(yall.p, y, n);
-    (void)hipMemset(m1.p, 0, IC_MLP_NPARAM * sizeof(float));
-    (void)hipMemset(m2.p, 0, IC_MLP_NPARAM * sizeof(float));
-    hipLaunchKernelGGL(k_normalise, dim3(((long)n * IC_MLP_IN + 255) / 256), dim3(256), 0, s, rawd.p, mean.p, istd.p,
-                       n, xall.p);
-    hipLaunchKernelGGL(k_to_bf16, dim3((IC_MLP_NPARAM + 255) / 256), dim3(256), 0, s, w.p, wb.p, (long)IC_MLP_NPARAM);
-    // deterministic shuffle per epoch (xorshift on the host), rows gathered by copies
+    // per-feature z-score statistics of the training set (fp64)
+    hipLaunchKernelGGL((k_stats<true>), dim3(IC_MLP_IN / STAT_C), dim3(1024), 0, s, (const float *)rawd.p, n, stat.p,
+                       stat.p + IC_MLP_IN);
+    hipLaunchKernelGGL((k_stats<false>), dim3(IC_MLP_IN / STAT_C), dim3(1024), 0, s, (const float *)rawd.p, n, stat.p,
+                       stat.p + IC_MLP_IN);
+    const int B = hp.batch;
+    const long nbatch = n / B;
+    Buf<uint16_t> xall((size_t)n * IC_MLP_IN), xb((size_t)B * IC_MLP_IN);
+    Buf<uint8_t> yall(n);
+    Buf<long> orderd(n);
+    Buf<double> lossacc(std::max(nbatch, 1L));           // per-minibatch loss sums, read once per epoch
+    Pass pass(B);
+    long npos = 0;
+    for (long b = 0; b < n; ++b) npos += y[b] ? 1 : 0;
+    const float pw = hp.pos_weight > 0.f ? hp.pos_weight : (npos > 0 ? (float)(n - npos) / (float)npos : 1.f);
+    // deterministic shuffle per epoch (xorshift on the host)
     std::vector<long> order(n);
     for (long b = 0; b < n; ++b) order[b] = b;
     uint64_t st = hp.seed * 2654435761ull + 88172645463325252ull;
@@ -751,31 +915,63 @@ void mlp_train(const float *raw, const uint8_t *y, long n, const MlpHparams &hp,
         st ^= st << 17;
         return st;
     };
-    long t = 0;
-    std::vector<double> lsums(std::max(nbatch, 1L));
-    for (int ep = 0; ep < hp.epochs; ++ep) {
+    auto shuffle = [&]() {
         for (long b = n - 1; b > 0; --b) std::swap(order[b], order[rnd() % (uint64_t)(b + 1)]);
+    };
+    if (hp.epochs > 0) shuffle();                        // while the statistics run
+    std::vector<double> stat_h(2 * IC_MLP_IN);
+    D2H(stat_h.data(), stat.p, 2 * IC_MLP_IN * sizeof(double));
+    std::vector<float> mean_h(IC_MLP_IN), std_h(IC_MLP_IN), istd_h(IC_MLP_IN);
+    for (int f = 0; f < IC_MLP_IN; ++f) {
+        mean_h[f] = (float)stat_h[f];
+        double sd = std::sqrt(stat_h[IC_MLP_IN + f] / (double)n);
+        if (!(sd > 1e-6)) sd = 1.0;
+        std_h[f] = (float)sd;
+        istd_h[f] = 1.0f / std_h[f];
+    }
+    H2D(mean.p, mean_h.data(), IC_MLP_IN * sizeof(float));
+    H2D(istd.p, istd_h.data(), IC_MLP_IN * sizeof(float));
+    H2D(w.p, params, IC_MLP_NPARAM * sizeof(float));
+    H2D(yall.p, y, n);
+    (void)hipMemset(m1.p, 0, IC_MLP_NPARAM * sizeof(float));
+    (void)hipMemset(m2.p, 0, IC_MLP_NPARAM * sizeof(float));
+    hipLaunchKernelGGL(k_normalise, dim3(((long)n * IC_MLP_IN + 255) / 256), dim3(256), 0, s, rawd.p, mean.p, istd.p,
+                       n, xall.p);
+    pass.pack(s, w.p);
+    std::vector<double> lsums(std::max(nbatch, 1L));
+    auto read_losses = [&](int ep) {                     // an epoch's minibatch losses, summed in batch order
+        D2H(lsums.data(), lossacc.p, nbatch * sizeof(double));
+        double lsum = 0.0;
+        for (long i = 0; i < nbatch; ++i) lsum += lsums[i];
+        if (loss_epochs) loss_epochs[ep] = (float)(lsum / (double)(nbatch * B));
+    };
+    long t = 0;
+    for (int ep = 0; ep < hp.epochs; ++ep) {
+        if (ep > 0) {
+            shuffle();                                   // while the last epoch's steps run
+            read_losses(ep - 1);
+        }
         H2D(orderd.p, order.data(), n * sizeof(long));
         long q = 0;
         for (long b0 = 0; b0 + B <= n; b0 += B, ++q) {
-            hipLaunchKernelGGL(k_gather, dim3(((long)B * IC_MLP_IN + 255) / 256), dim3(256), 0, s, xall.p, yall.p,
-                               orderd.p, b0, B, xb.p, yb.p);
-            fwd_bwd(s, B, xb.p, yb.p, pw, w.p, wb.p, grad.p, loss.p, H1, H2, dz, dZ2, dZ2b, dH1, dZ1, dZ1b, work.p);
-            hipLaunchKernelGGL(k_loss_sum, dim3(1), dim3(256), 0, s, (const float *)loss.p, B, lossacc.p, q);
             ++t;
             const float c1 = 1.f - std::pow(hp.beta1, (float)t), c2 = 1.f - std::pow(hp.beta2, (float)t);
-            hipLaunchKernelGGL(k_adam, dim3((IC_MLP_NPARAM + 255) / 256), dim3(256), 0, s, w.p, wb.p, grad.p, m1.p,
-                               m2.p, IC_MLP_NPARAM, hp.lr, hp.beta1, hp.beta2, hp.eps, c1, c2);
+            StepArgs st{};
+            st.w = w.p;
+            st.m1 = m1.p;
+            st.m2 = m2.p;
+            st.lr = hp.lr;
+            st.b1 = hp.beta1;
+            st.b2 = hp.beta2;
+            st.eps = hp.eps;
+            st.c1 = c1;
+            st.c2 = c2;
+            st.loss_out = lossacc.p + q;
+            pass.run(s, xall.p, orderd.p + b0, yall.p, pw, w.p, xb.p, st);
         }
-        // the epoch's minibatch losses, summed in batch order
-        if (q > 0 && hipMemcpy(lsums.data(), lossacc.p, q * sizeof(double), hipMemcpyDeviceToHost) != hipSuccess)
-            throw std::runtime_error("hipMemcpy failed");
-        double lsum = 0.0;
-        for (long i = 0; i < q; ++i) lsum += lsums[i];
-        if (loss_epochs) loss_epochs[ep] = q ? (float)(lsum / (double)(q * B)) : 0.f;
     }
-    if (hipMemcpy(params, w.p, IC_MLP_NPARAM * sizeof(float), hipMemcpyDeviceToHost) != hipSuccess)
-        throw std::runtime_error("hipMemcpy failed");
+    if (hp.epochs > 0) read_losses(hp.epochs - 1);
+    D2H(params, w.p, IC_MLP_NPARAM * sizeof(float));
     std::memcpy(mean_out, mean_h.data(), IC_MLP_IN * sizeof(float));
     std::memcpy(std_out, std_h.data(), IC_MLP_IN * sizeof(float));
 }
