@@ -44,6 +44,15 @@ struct KArgs {
     double *divb;              // parabolic cleaning: div B of the stage input per slot and cell
     double divb_cd;            // parabolic cleaning coefficient C_d (0 = off)
     int nv;                    // conserved variables per cell (8, or 9 with the tracer)
+    double *slabs_mid;         // ghost slabs of the second stage, filled with the first's (NULL: not)
+};
+
+// CFL step of each member, for k_dt or at the end of k_sample (mbeg NULL: none)
+struct DtArgs {
+    const int *mbeg, *mend;    // a member's part of the work list
+    double cfl, dt_fixed;      // dt_fixed > 0: in place of cfl / (largest rate)
+    const double *tend;
+    double *dt_last;
 };
 
 // CFL maxima are kept per block and k-part: rate[slot * KSPLIT_MAX + part]
@@ -181,12 +190,10 @@ struct Launchers {
     void (*indicator)(dim3, hipStream_t, const KArgs &, int8_t *, const IndicatorParams &);
     void (*move)(dim3, hipStream_t, const KArgs &, double *, const MoveTask *, int);
     void (*sample)(dim3, hipStream_t, const KArgs &, const SampleDesc *, int, double *, double *, int *, int, int,
-                   double *, long *);
+                   double *, long *, const DtArgs &);
 };
 bool get_launchers(int bi, int bj, int bk, int nv, Launchers *out);
-void launch_dt(hipStream_t s, const KArgs &a, const int *mbeg, const int *mend, int nm, double cfl,
-               double dt_fixed, const double *tend, double *dt_last);
-void launch_time(hipStream_t s, double *t, const double *dt, long *nsteps, int nm);
+void launch_dt(hipStream_t s, const KArgs &a, const DtArgs &d, int nm);
 
 // kernel entry points (stage.hip: k_stage and its launcher; kernels.hip: the rest)
 template <int BI, int BJ, int BK, int NV, int W, int LIM> __global__ void k_stage(KArgs a);
@@ -207,8 +214,6 @@ template <int BI, int BJ, int BK, int NV>
 __global__ void k_move(KArgs a, double *Unew, const MoveTask *tasks, int ntasks);
 template <int BI, int BJ, int BK, int NV>
 __global__ void k_sample(KArgs a, const SampleDesc *sd, int nmembers, double *out, double *ring,
-                         int *ring_count, int ring_cap, int record, double *t_step, long *nsteps);
+                         int *ring_count, int ring_cap, int record, double *t_step, long *nsteps, DtArgs dt_next);
 
-__global__ void k_dt(KArgs a, const int *mbeg, const int *mend, int nmembers, double cfl,
-                     double dt_fixed, const double *tend, double *dt_last);
-__global__ void k_time(double *t, const double *dt, long *nsteps, int nmembers);
+__global__ void k_dt(KArgs a, DtArgs d, int nmembers);

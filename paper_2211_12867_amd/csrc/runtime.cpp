@@ -374,6 +374,7 @@ struct ic_sim {
     DBuf<int> ring_count;
     int ring_cap = 1 << 16;
     long slab_stride = 0, reg_stride = 0;
+    long mid_slabs = 0;             // doubles from the slabs to a second set (slabs_mid), 0: there is none
 
     // host mirrors of the task lists
     int n_items = 0;
@@ -1144,7 +1145,10 @@ void rebuild(ic_sim *s)
             s->graph_dirty = true;
         }
     };
-    grow(s->slabs, (size_t)std::max(nslab, 1) * s->slab_stride);
+    // Without refinement every slab is an inner-boundary one, which depends on
+    // t and dt alone: both stages' are then filled in one launch (ghosts_at_once).
+    s->mid_slabs = s->max_level == 1 ? (long)std::max(nslab, 1) * s->slab_stride : 0;
+    grow(s->slabs, (size_t)std::max(nslab, 1) * s->slab_stride * (s->mid_slabs ? 2 : 1));
     grow(s->freg, (size_t)std::max(s->n_regs, 1) * s->reg_stride);
     grow(s->slab_tasks, all.size() + 1);
     grow(s->rf_tasks, rf.size() + 1);
@@ -1218,6 +1222,7 @@ KArgs base_args(ic_sim *s)
     a.divb = s->divb.p;
     a.divb_cd = s->phys.divb_cd;
     a.nv = s->nv;
+    a.slabs_mid = nullptr;
     return a;
 }
 
@@ -1294,12 +1299,33 @@ void fill_ghosts(ic_sim *s, double *Uin, double tfrac)
     if (s->max_level > 1) s->L.slabs(dim3(slab_grid(s, 1)), s->stream, a, s->slab_tasks.p, s->slab_ranges.p + 2, 1);
 }
 
+// Ghosts of both stages of a step in one launch (no refinement): a launch of
+// 4 to 5 us and the gap before it less in a step of 40 to 110 us on up to 320
+// blocks; nothing to fill in a periodic box.
+void ghosts_at_once(ic_sim *s)
+{
+    if (s->pass_hi[0] == s->pass_lo[0]) return;
+    KArgs a = base_args(s);
+    a.U = s->U.p;
+    a.tfrac = 0.0;
+    a.slabs_mid = a.slabs + s->mid_slabs;
+    s->L.slabs(dim3(slab_grid(s, 0)), s->stream, a, s->slab_tasks.p, s->slab_ranges.p, 0);
+}
+
+// arguments of a kernel that reads Uin with its ghosts
+KArgs stage_args(ic_sim *s, double *Uin)
+{
+    KArgs a = base_args(s);
+    a.U = Uin;
+    if (Uin == s->Us.p) a.slabs += s->mid_slabs;
+    return a;
+}
+
 void stage(ic_sim *s, double *Uin, double *Ubase, double *Uout, double alpha, int want_rate)
 {
     // with the cleaning, the CFL maxima and the output check follow it (clean)
     if (s->phys.divb_cd > 0.0) want_rate = 0;
-    KArgs a = base_args(s);
-    a.U = Uin;
+    KArgs a = stage_args(s, Uin);
     a.Ubase = Ubase;
     a.Uout = Uout;
     a.alpha = alpha;
@@ -1326,8 +1352,7 @@ void stage(ic_sim *s, double *Uin, double *Ubase, double *Uout, double alpha, in
 // div B of the stage input Uin (ghosts filled) into s->divb
 void divb(ic_sim *s, double *Uin)
 {
-    KArgs a = base_args(s);
-    a.U = Uin;
+    KArgs a = stage_args(s, Uin);
     s->L.divb(dim3(quant_grid(s->n_items, 1 << 30)), s->stream, a);
 }
 
@@ -1335,8 +1360,7 @@ void divb(ic_sim *s, double *Uin)
 // div B in s->divb); want_rate: the stage's output check and CFL maxima here
 void clean(ic_sim *s, double *Uin, double *Uout, double alpha, int want_rate)
 {
-    KArgs a = base_args(s);
-    a.U = Uin;
+    KArgs a = stage_args(s, Uin);
     a.Uout = Uout;
     a.alpha = alpha;
     a.want_rate = want_rate;
@@ -1347,8 +1371,7 @@ void clean(ic_sim *s, double *Uin, double *Uout, double alpha, int want_rate)
 // work-group per work item
 void predictor(ic_sim *s, double *Uin, double *Uout)
 {
-    KArgs a = base_args(s);
-    a.U = Uin;
+    KArgs a = stage_args(s, Uin);
     a.Ubase = Uin;
     a.Uout = Uout;
     a.alpha = 0.5;
@@ -1363,31 +1386,39 @@ void enqueue_rate(ic_sim *s)
     s->L.rate(dim3(grid_for(s->n_items, 16384)), s->stream, a);
 }
 
-// sample at the point; end_step: the same launch first ends the step (t += dt)
-void enqueue_sample(ic_sim *s, int record, bool end_step = false)
+DtArgs dt_args(const ic_sim *s, double dt_fixed_code)
+{
+    return DtArgs{s->mbeg.p, s->mend.p, s->phys.cfl, dt_fixed_code, s->tend.p, s->dt_last.p};
+}
+
+// sample at the point; end_step: the same launch first ends the step (t += dt);
+// d: and then sets the next step's dt
+void enqueue_sample(ic_sim *s, int record, bool end_step = false, const DtArgs &d = DtArgs{})
 {
     KArgs a = base_args(s);
     a.U = s->U.p;
     s->L.sample(dim3(s->nm), s->stream, a, s->sdesc.p, s->nm, s->sout.p, s->ring.p, s->ring_count.p,
-                s->ring_cap, record, end_step ? s->t.p : nullptr, end_step ? s->nsteps.p : nullptr);
+                s->ring_cap, record, end_step ? s->t.p : nullptr, end_step ? s->nsteps.p : nullptr, d);
 }
 
-void enqueue_step(ic_sim *s, double dt_fixed_code, bool record)
+// One step, which records the sample; first / last: of the steps enqueued
+// together, the ones between which the sample's launch sets dt
+void enqueue_step(ic_sim *s, double dt_fixed_code, bool first, bool last)
 {
-    KArgs a = base_args(s);
-    launch_dt(s->stream, a, s->mbeg.p, s->mend.p, s->nm, s->phys.cfl, dt_fixed_code, s->tend.p, s->dt_last.p);
-    const bool cleaning = s->phys.divb_cd > 0.0;
-    fill_ghosts(s, s->U.p, 0.0);
+    const DtArgs d = dt_args(s, dt_fixed_code);
+    if (first) launch_dt(s->stream, base_args(s), d, s->nm);
+    const bool cleaning = s->phys.divb_cd > 0.0, at_once = s->mid_slabs > 0;
+    if (at_once) ghosts_at_once(s);
+    else fill_ghosts(s, s->U.p, 0.0);
     if (cleaning) divb(s, s->U.p);
     if (s->phys.scheme == IC_SCHEME_HANCOCK) predictor(s, s->U.p, s->Us.p);
     else stage(s, s->U.p, s->U.p, s->Us.p, 0.5, 0);
     if (cleaning) clean(s, s->U.p, s->Us.p, 0.5, 0);
-    fill_ghosts(s, s->Us.p, 0.5);
+    if (!at_once) fill_ghosts(s, s->Us.p, 0.5);
     if (cleaning) divb(s, s->Us.p);
     stage(s, s->Us.p, s->U.p, s->U.p, 1.0, 1);
     if (cleaning) clean(s, s->Us.p, s->U.p, 1.0, 1);
-    if (record) enqueue_sample(s, 1, true);       // ends the step and records the sample
-    else launch_time(s->stream, s->t.p, s->dt.p, s->nsteps.p, s->nm);
+    enqueue_sample(s, 1, true, last ? DtArgs{} : d);
 }
 
 // Steps per replay of the multi-step graph: one graph launch per step leaves
@@ -1411,7 +1442,7 @@ void release_graphs(ic_sim *s)
 void run_steps(ic_sim *s, double dt_fixed_code, int nsteps)
 {
     if (s->timing || !s->use_graph) {
-        for (int q = 0; q < nsteps; ++q) enqueue_step(s, dt_fixed_code, true);
+        for (int q = 0; q < nsteps; ++q) enqueue_step(s, dt_fixed_code, q == 0, q == nsteps - 1);
         return;
     }
     if (s->graph_dirty) {
@@ -1424,7 +1455,7 @@ void run_steps(ic_sim *s, double dt_fixed_code, int nsteps)
         G.exec = nullptr;
         hipGraph_t g;
         HIPCHECK(hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal));
-        for (int q = 0; q < nsteps; ++q) enqueue_step(s, dt_fixed_code, true);
+        for (int q = 0; q < nsteps; ++q) enqueue_step(s, dt_fixed_code, q == 0, q == nsteps - 1);
         HIPCHECK(hipStreamEndCapture(s->stream, &g));
         HIPCHECK(hipGraphInstantiate(&G.exec, g, nullptr, nullptr, 0));
         HIPCHECK(hipGraphDestroy(g));
@@ -2601,7 +2632,7 @@ ic_status ic_sample(ic_sim *s, int member, double r_au, double colat_deg, double
         KArgs a = base_args(s);
         a.U = s->U.p;
         s->L.sample(dim3(s->nm), s->stream, a, tmp.p, s->nm, s->sout.p, s->ring.p, s->ring_count.p, s->ring_cap, 0,
-                    nullptr, nullptr);
+                    nullptr, nullptr, DtArgs{});
         HIPCHECK(hipMemcpyAsync(prim_out, s->sout.p + member * 8, 8 * sizeof(double), hipMemcpyDeviceToHost, s->stream));
         HIPCHECK(hipStreamSynchronize(s->stream));
         tmp.release();
@@ -3058,8 +3089,7 @@ ic_status ic_autotune(ic_sim *s, const char *cache_path, int reps, ic_tune_info 
         }
         if (!res.from_cache) {
             // stage 1 reads U, writes the scratch stage state: the sim's state is untouched
-            KArgs a = base_args(s);
-            launch_dt(s->stream, a, s->mbeg.p, s->mend.p, s->nm, s->phys.cfl, 0.0, s->tend.p, s->dt_last.p);
+            launch_dt(s->stream, base_args(s), dt_args(s, 0.0), s->nm);
             fill_ghosts(s, s->U.p, 0.0);
             double best = 1e300;
             int dev = 0, cus = 256;
