@@ -2,8 +2,6 @@
 #pragma once
 #include "kernels.h"
 
-#define NT 256   // threads per work-group of the block kernels
-
 template <class S>
 __device__ inline size_t cidx(int slot, int v, int i, int j, int k)
 {

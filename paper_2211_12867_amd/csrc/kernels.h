@@ -55,6 +55,8 @@ struct DtArgs {
     double *dt_last;
 };
 
+#define NT 256   // threads per work-group of the block kernels
+
 // CFL maxima are kept per block and k-part: rate[slot * KSPLIT_MAX + part]
 // (a block of up to KSPLIT_MAX planes along phi can give each plane its own
 // work-group)
