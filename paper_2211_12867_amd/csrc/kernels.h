@@ -73,39 +73,6 @@ struct Shape {
                                                        : (BI * BK > BJ * BK ? BI * BK : BJ * BK));
 };
 
-// Address of variable v of the cell (i, j, k) of block `slot`, where at most
-// one index may lie in the two ghost layers: interior, same-level neighbour,
-// outflow copy of the edge cell, or ghost slab.  Within a block or a slab the
-// cells of one (i, j) plane are contiguous in i, then j.
-template <class S>
-__device__ inline const double *ghosted_addr(const double *__restrict__ U, const BlockDesc *__restrict__ desc,
-                                             const double *__restrict__ slabs, long slab_stride, int slot, int v,
-                                             int i, int j, int k)
-{
-    int idx[3] = {i, j, k};
-    int d = -1;
-    if (i < 0 || i >= S::B0) d = 0;
-    else if (j < 0 || j >= S::B1) d = 1;
-    else if (k < 0 || k >= S::B2) d = 2;
-    if (d < 0) return U + (size_t)slot * S::NV * S::NC + (size_t)v * S::NC + i + S::B0 * (j + S::B1 * k);
-    const int Bd = S::dim(d);
-    const int side = idx[d] >= Bd ? 1 : 0;
-    const int l = side ? idx[d] - Bd : idx[d] + 2;
-    const int code = desc[slot].nbr[2 * d + side];
-    if (code >= 0) {
-        idx[d] = side ? l : Bd - 2 + l;
-        return U + (size_t)code * S::NV * S::NC + (size_t)v * S::NC + idx[0] + S::B0 * (idx[1] + S::B1 * idx[2]);
-    }
-    if (code == NBR_OUTFLOW) {
-        idx[d] = side ? Bd - 1 : 0;
-        return U + (size_t)slot * S::NV * S::NC + (size_t)v * S::NC + idx[0] + S::B0 * (idx[1] + S::B1 * idx[2]);
-    }
-    const int s = nbr_slab(code);
-    const int a = idx[tan1(d)], b = idx[tan2(d)];
-    const int FA = S::dim(tan1(d)), FB = S::dim(tan2(d));
-    return slabs + (size_t)s * slab_stride + ((size_t)(v * 2 + l) * FB + b) * FA + a;
-}
-
 // The six face codes of a block (BlockDesc::nbr), held in scalar registers.
 struct Faces {
     int n0, n1, n2, n3, n4, n5;
@@ -128,8 +95,7 @@ DEV int face_code(const Faces &nb, int f)
 // Address of variable v of the cell (i, j, k) of block `slot`, where at most
 // one index lies in the two ghost layers (interior, same-level neighbour,
 // outflow copy of the edge cell or ghost slab), with the block's face codes
-// in registers: the cases of ghosted_addr without a descriptor load per
-// lane.  With i = j = 0 it gives the start of a k-plane, whose cells are
+// in registers.  With i = j = 0 it gives the start of a k-plane, whose cells are
 // contiguous in i, then j, in a block, a slab and an outflow copy.
 template <class S>
 DEV const double *cell_addr(const double *__restrict__ U, const double *__restrict__ slabs, long slab_stride,
@@ -158,12 +124,38 @@ DEV const double *cell_addr(const double *__restrict__ U, const double *__restri
     return slabs + (size_t)nbr_slab(code) * slab_stride + ((size_t)(v * 2 + l) * FB + b) * FA + a;
 }
 
+// A cell's variables: variable v at p[v * st].  The cases of cell_addr worked
+// out once for all variables, with selects: a kernel that asks cell_addr for
+// each variable of seven cells is mostly its branches (prolongation slabs:
+// 130 KB of code and 15.7 us a launch of the level-4 run, now 24 KB and 10.2;
+// predictor 14.4 -> 12.3, div B 4.9 -> 4.1 on 45 blocks of 12x8x12).
+struct CellRef {
+    const double *p;
+    int st;
+    DEV double operator[](int v) const { return p[(size_t)v * st]; }
+};
+
 template <class S>
-__device__ inline double ghosted(const double *__restrict__ U, const BlockDesc *__restrict__ desc,
-                                 const double *__restrict__ slabs, long slab_stride, int slot, int v,
-                                 int i, int j, int k)
+DEV CellRef own_cell(const KArgs &a, int slot, int i, int j, int k)
 {
-    return *ghosted_addr<S>(U, desc, slabs, slab_stride, slot, v, i, j, k);
+    return CellRef{a.U + (size_t)slot * S::NV * S::NC + i + S::B0 * (j + S::B1 * k), S::NC};
+}
+
+// the cell next to (i, j, k) of block `slot` along D on side O (0 low, 1 high)
+template <class S, int D, int O>
+DEV CellRef next_cell(const KArgs &a, int slot, const Faces &nb, int i, int j, int k)
+{
+    constexpr int Bd = S::dim(D), FA = S::dim(tan1(D)), FB = S::dim(tan2(D));
+    int x[3] = {i, j, k};
+    const int pos = (size_t)x[tan2(D)] * FA + x[tan1(D)], code = face_code(nb, 2 * D + O);
+    const bool out = O ? x[D] == Bd - 1 : x[D] == 0;
+    const bool slab = out && code < 0 && code != NBR_OUTFLOW;
+    // inside, the same-level neighbour's first or last, or the edge cell itself (outflow)
+    if (!out) x[D] += O ? 1 : -1;
+    else if (code >= 0) x[D] = O ? 0 : Bd - 1;
+    const double *u = a.U + (size_t)(out && code >= 0 ? code : slot) * S::NV * S::NC + x[0] + S::B0 * (x[1] + S::B1 * x[2]);
+    const double *g = a.slabs + (size_t)(slab ? nbr_slab(code) : 0) * a.slab_stride + (O ? 0 : FA * FB) + pos;
+    return CellRef{slab ? g : u, slab ? 2 * FA * FB : S::NC};
 }
 
 // Refinement criteria: the Sect. 3.2 shock criterion, the Sect. 3.1 tracer

@@ -28,6 +28,20 @@ struct Prolong {
     DEV double value(int o, int v) const { return ok ? linear(o, v) : uc[v]; }
 };
 
+// a cell of block `slot` and its six neighbours
+template <class S>
+struct CellStar {
+    CellRef own, lo[3], hi[3];
+    DEV CellStar(const KArgs &a, int slot, const Faces &nb, const int c[3])
+        : own(own_cell<S>(a, slot, c[0], c[1], c[2])),
+          lo{next_cell<S, 0, 0>(a, slot, nb, c[0], c[1], c[2]), next_cell<S, 1, 0>(a, slot, nb, c[0], c[1], c[2]),
+             next_cell<S, 2, 0>(a, slot, nb, c[0], c[1], c[2])},
+          hi{next_cell<S, 0, 1>(a, slot, nb, c[0], c[1], c[2]), next_cell<S, 1, 1>(a, slot, nb, c[0], c[1], c[2]),
+             next_cell<S, 2, 1>(a, slot, nb, c[0], c[1], c[2])}
+    {
+    }
+};
+
 template <int BI, int BJ, int BK, int NV>
 DEV void prolong_setup(const KArgs &a, int src, const int cl[3], const int cw[3], const LevelGeo &cg,
                        const LevelGeo &lg, const int g0[3], Prolong<NV> &P)
@@ -35,16 +49,13 @@ DEV void prolong_setup(const KArgs &a, int src, const int cl[3], const int cw[3]
     using S = Shape<BI, BJ, BK, NV>;
     const double idm[3] = {cg.r[cw[0] + 2].idm, cg.t[cw[1] + 2].idm, cg.p[cw[2] + 2].idm};
     const double idp[3] = {cg.r[cw[0] + 2].idp, cg.t[cw[1] + 2].idp, cg.p[cw[2] + 2].idp};
+    const CellStar<S> q(a, src, load_faces(a.desc, src), cl);
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        P.uc[v] = ghosted<S>(a.U, a.desc, a.slabs, a.slab_stride, src, v, cl[0], cl[1], cl[2]);
+        P.uc[v] = q.own[v];
 #pragma unroll
         for (int e = 0; e < 3; ++e) {
-            int lm[3] = {cl[0], cl[1], cl[2]}, lp[3] = {cl[0], cl[1], cl[2]};
-            lm[e] -= 1;
-            lp[e] += 1;
-            const double um = ghosted<S>(a.U, a.desc, a.slabs, a.slab_stride, src, v, lm[0], lm[1], lm[2]);
-            const double up = ghosted<S>(a.U, a.desc, a.slabs, a.slab_stride, src, v, lp[0], lp[1], lp[2]);
+            const double um = q.lo[e][v], up = q.hi[e][v];
             const double sa = (P.uc[v] - um) * idm[e], sb = (up - P.uc[v]) * idp[e];
             P.sl[e][v] = sa * sb > 0.0 ? copysign(fmin(fabs(sa), fabs(sb)), sa) : 0.0;
         }
@@ -114,17 +125,14 @@ DEV void prolong_parent(const KArgs &a, const SlabTask *tkp, int c)
                               {lg.t[g0[1] + 2].poff, lg.t[g0[1] + 3].poff},
                               {lg.p[g0[2] + 2].poff, lg.p[g0[2] + 3].poff}};
     double P[NV][4];
+    const CellStar<S> star(a, cs, cnb, cl);
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        const double uc = *cell_addr<S>(a.U, a.slabs, a.slab_stride, cs, cnb, v, cl[0], cl[1], cl[2]);
+        const double uc = star.own[v];
         P[v][0] = uc;
 #pragma unroll
         for (int e = 0; e < 3; ++e) {
-            int lm[3] = {cl[0], cl[1], cl[2]}, lp[3] = {cl[0], cl[1], cl[2]};
-            lm[e] -= 1;
-            lp[e] += 1;
-            const double um = *cell_addr<S>(a.U, a.slabs, a.slab_stride, cs, cnb, v, lm[0], lm[1], lm[2]);
-            const double up = *cell_addr<S>(a.U, a.slabs, a.slab_stride, cs, cnb, v, lp[0], lp[1], lp[2]);
+            const double um = star.lo[e][v], up = star.hi[e][v];
             const double sa = (uc - um) * idm[e], sb = (up - uc) * idp[e];
             P[v][1 + e] = sa * sb > 0.0 ? copysign(fmin(fabs(sa), fabs(sb)), sa) : 0.0;
         }
@@ -519,16 +527,16 @@ __global__ void __launch_bounds__(NT) k_reflux(KArgs a, const RefluxTask *tasks,
 // reconstructed lower and upper face states, plus the sources at the cell
 // state; no interface solver and no reflux (the corrector, a stage-kernel
 // launch from U*, is conservative).  One thread per cell, a block's cells over
-// gridDim.y work-groups; neighbours along each axis through cell_addr (one
-// index at most in the ghost layers).  Floors and the input check as in k_stage.
-// 45 blocks of 12x8x12: 37.9 us with a work-group a block, 14.4 with five.
+// gridDim.y work-groups; neighbours along each axis through next_cell.  Floors and the input check as in k_stage.
+// 45 blocks of 12x8x12: 37.9 us with a work-group a block, 14.4 with five, 12.3
+// with the neighbours' addresses worked out once for all variables.
 // ---------------------------------------------------------------------------
 template <class S>
-DEV void prim_at(const KArgs &a, int slot, const Faces &nb, int i, int j, int k, double *w)
+DEV void prim_at(const KArgs &a, const CellRef &c, double *w)
 {
     double u[S::NV];
 #pragma unroll
-    for (int v = 0; v < S::NV; ++v) u[v] = *cell_addr<S>(a.U, a.slabs, a.slab_stride, slot, nb, v, i, j, k);
+    for (int v = 0; v < S::NV; ++v) u[v] = c[v];
     cons_to_prim<false, S::NV>(u, w, a.gas);
 }
 
@@ -551,7 +559,7 @@ __global__ void __launch_bounds__(NT) k_hancock(KArgs a)
         for (int c = blockIdx.y * NT + threadIdx.x; c < S::NC; c += gridDim.y * NT) {
             const int i = c % BI, j = (c / BI) % BJ, k = c / (BI * BJ);
             double w0[NV], acc[NV];
-            prim_at<S>(a, slot, nb, i, j, k, w0);
+            prim_at<S>(a, own_cell<S>(a, slot, i, j, k), w0);
             if (badc < 0 && unphysical<NV>(w0)) badc = c;
 #pragma unroll
             for (int v = 0; v < NV; ++v) acc[v] = 0.0;
@@ -560,8 +568,8 @@ __global__ void __launch_bounds__(NT) k_hancock(KArgs a)
             const RecP pk = lg.p[o2 + k + 2];
             {   // r
                 double wm[NV], wp[NV], lo[NV], hi[NV], fl[NV], fh[NV];
-                prim_at<S>(a, slot, nb, i - 1, j, k, wm);
-                prim_at<S>(a, slot, nb, i + 1, j, k, wp);
+                prim_at<S>(a, next_cell<S, 0, 0>(a, slot, nb, i, j, k), wm);
+                prim_at<S>(a, next_cell<S, 0, 1>(a, slot, nb, i, j, k), wp);
                 reconstruct<LIM, NV>(wm, w0, wp, slope_scale<LIM>(rr.idm), slope_scale<LIM>(rr.idp), rr.idc,
                                      rr.hm, rr.hp, lo, hi);
                 phys_flux<0, NV>(lo, fl, gs);
@@ -571,8 +579,8 @@ __global__ void __launch_bounds__(NT) k_hancock(KArgs a)
             }
             {   // theta
                 double wm[NV], wp[NV], lo[NV], hi[NV], fl[NV], fh[NV];
-                prim_at<S>(a, slot, nb, i, j - 1, k, wm);
-                prim_at<S>(a, slot, nb, i, j + 1, k, wp);
+                prim_at<S>(a, next_cell<S, 1, 0>(a, slot, nb, i, j, k), wm);
+                prim_at<S>(a, next_cell<S, 1, 1>(a, slot, nb, i, j, k), wp);
                 reconstruct<LIM, NV>(wm, w0, wp, slope_scale<LIM>(tt.idm), slope_scale<LIM>(tt.idp), tt.idc,
                                      tt.hm, tt.hp, lo, hi);
                 phys_flux<1, NV>(lo, fl, gs);
@@ -583,8 +591,8 @@ __global__ void __launch_bounds__(NT) k_hancock(KArgs a)
             }
             {   // phi
                 double wm[NV], wp[NV], lo[NV], hi[NV], fl[NV], fh[NV];
-                prim_at<S>(a, slot, nb, i, j, k - 1, wm);
-                prim_at<S>(a, slot, nb, i, j, k + 1, wp);
+                prim_at<S>(a, next_cell<S, 2, 0>(a, slot, nb, i, j, k), wm);
+                prim_at<S>(a, next_cell<S, 2, 1>(a, slot, nb, i, j, k), wp);
                 reconstruct<LIM, NV>(wm, w0, wp, slope_scale<LIM>(pk.idm), slope_scale<LIM>(pk.idp), pk.idc,
                                      pk.hm, pk.hp, lo, hi);
                 phys_flux<2, NV>(lo, fl, gs);
@@ -650,16 +658,16 @@ __global__ void __launch_bounds__(NT) k_divb(KArgs a)
             const RecR rr = lg.r[o0 + i + 2];
             const RecT tt = lg.t[o1 + j + 2];
             const RecP pk = lg.p[o2 + k + 2];
-            const double *U = a.U;
-            const double b0 = *cell_addr<S>(U, a.slabs, a.slab_stride, slot, nb, 5, i, j, k);
-            const double b1 = *cell_addr<S>(U, a.slabs, a.slab_stride, slot, nb, 6, i, j, k);
-            const double b2 = *cell_addr<S>(U, a.slabs, a.slab_stride, slot, nb, 7, i, j, k);
-            const double rl = 0.5 * (*cell_addr<S>(U, a.slabs, a.slab_stride, slot, nb, 5, i - 1, j, k) + b0);
-            const double rh = 0.5 * (b0 + *cell_addr<S>(U, a.slabs, a.slab_stride, slot, nb, 5, i + 1, j, k));
-            const double tl = 0.5 * (*cell_addr<S>(U, a.slabs, a.slab_stride, slot, nb, 6, i, j - 1, k) + b1);
-            const double th = 0.5 * (b1 + *cell_addr<S>(U, a.slabs, a.slab_stride, slot, nb, 6, i, j + 1, k));
-            const double pl = 0.5 * (*cell_addr<S>(U, a.slabs, a.slab_stride, slot, nb, 7, i, j, k - 1) + b2);
-            const double ph = 0.5 * (b2 + *cell_addr<S>(U, a.slabs, a.slab_stride, slot, nb, 7, i, j, k + 1));
+            const CellRef own = own_cell<S>(a, slot, i, j, k);
+            const double b0 = own[5];
+            const double b1 = own[6];
+            const double b2 = own[7];
+            const double rl = 0.5 * (next_cell<S, 0, 0>(a, slot, nb, i, j, k)[5] + b0);
+            const double rh = 0.5 * (b0 + next_cell<S, 0, 1>(a, slot, nb, i, j, k)[5]);
+            const double tl = 0.5 * (next_cell<S, 1, 0>(a, slot, nb, i, j, k)[6] + b1);
+            const double th = 0.5 * (b1 + next_cell<S, 1, 1>(a, slot, nb, i, j, k)[6]);
+            const double pl = 0.5 * (next_cell<S, 2, 0>(a, slot, nb, i, j, k)[7] + b2);
+            const double ph = 0.5 * (b2 + next_cell<S, 2, 1>(a, slot, nb, i, j, k)[7]);
             const double kf = rr.rt * tt.phf * pk.iw;
             double dv = rr.ap * rh - rr.am * rl;
             dv += rr.rt * tt.thp * th - rr.rt * tt.thm * tl;
