@@ -388,13 +388,15 @@ ic_status ic_mlp_infer(const float *raw, long n, const float *params, const floa
  * probabilities of ic_mlp_infer with every array on the device and no
  * allocation of any kind.  raw_dev [n x 512], params_dev [IC_MLP_NPARAM],
  * mean_dev and std_dev [512] (std must be positive; the values are not
- * checked on the host), prob_dev [n], which overlaps none of them: device
- * pointers owned by the caller.
+ * checked on the host), prob_dev [n]: device pointers owned by the caller.
+ * prob_dev may lie on inputs, which are read before they are written over
+ * (rows of raw_dev under it, or all rows where it lies on the network's arrays,
+ * then go through one work-group, which takes longer).
  * The work is enqueued on hip_stream (NULL = the null stream) and the call
  * returns without synchronising; prob_dev is valid once the stream has
- * completed it.  n may not exceed IC_MLP_NOALLOC_ROWS (IC_E_INVALID).  One
- * kernel launch; calls share no memory of the library, so calls on other
- * streams or threads may overlap.  Results equal ic_mlp_infer's bit for
+ * completed it.  n may not exceed IC_MLP_NOALLOC_ROWS (IC_E_INVALID).  Kernel
+ * launches alone (one, unless prob_dev lies on inputs); calls share no memory
+ * of the library, so calls on other streams or threads may overlap.  Results equal ic_mlp_infer's bit for
  * bit. */
 #define IC_MLP_NOALLOC_ROWS 4096
 ic_status ic_mlp_infer_noalloc(const float *raw_dev, long n, const float *params_dev, const float *mean_dev,

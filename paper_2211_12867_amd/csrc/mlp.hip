@@ -19,6 +19,7 @@
 #include <stdexcept>
 #include <string>
 #include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "devmem.h"
@@ -166,8 +167,10 @@ DEV_EPI float head_row(const uint16_t *H2, const float *w3, float b3)
     return s + b3;
 }
 
-// RAW: x is fp32 raw inputs, z-scored here with mean and std; else bf16, normalised
-template <bool RAW>
+// RAW: x is fp32 raw inputs, z-scored here with mean and std; else bf16, normalised.
+// HOLD: one work-group takes all rows (at most IC_MLP_NOALLOC_ROWS) and writes
+// the probabilities when it has read every input, so prob may lie on them.
+template <bool RAW, bool HOLD = false>
 __global__ void __launch_bounds__(NET_TH) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_infer(const void *x, const float *mean, const float *std, const float *P, int n, float *prob)
 {
@@ -175,6 +178,7 @@ k_infer(const void *x, const float *mean, const float *std, const float *P, int 
     __shared__ __attribute__((aligned(16))) uint16_t Hs[16 * NET_HP];
     __shared__ __attribute__((aligned(16))) uint16_t Gs[16 * NET_HP];
     __shared__ __attribute__((aligned(16))) float w3s[IC_MLP_HID];
+    __shared__ float held[HOLD ? IC_MLP_NOALLOC_ROWS : 1];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int col = wave * 16 + (lane & 15), row4 = (lane >> 4) * 4;
     const int ntile = (n + 15) / 16;
@@ -234,8 +238,12 @@ k_infer(const void *x, const float *mean, const float *std, const float *P, int 
         // Gs is written again two barriers on, Xs was last read one barrier ago
         if (tid < 16 && tile * 16 + tid < n) {
             const float s = head_row(&Gs[tid * NET_HP], w3s, b3);
-            prob[tile * 16 + tid] = 1.f / (1.f + expf(-s));
+            (HOLD ? held : prob)[tile * 16 + tid] = 1.f / (1.f + expf(-s));
         }
+    }
+    if constexpr (HOLD) {
+        __syncthreads();
+        for (int b = tid; b < n; b += NET_TH) prob[b] = held[b];
     }
 }
 
@@ -1005,16 +1013,38 @@ void mlp_infer(const float *raw, long n, const float *params, const float *mean,
 }
 
 // ---------------------------------------------------------------------------
-// inference without allocation: the one launch reads the caller's arrays and
-// writes the probabilities, with no intermediate value in device memory
+// inference without allocation: the launch reads the caller's arrays and writes
+// the probabilities, with no intermediate value in device memory.  Where the
+// probabilities overlie inputs (a caller that is done with them), no
+// work-group may write before the inputs under its rows are read: the rows of
+// raw under prob go first, in one work-group that holds their results back
+// (prob's n values lie on at most 9 rows when n is 4,096); the other rows'
+// probabilities then fall on those rows or outside raw.  On the network's own
+// arrays all rows go that way.
 // ---------------------------------------------------------------------------
 void mlp_infer_noalloc(const float *raw, long n, const float *params, const float *mean, const float *std,
                        float *prob, hipStream_t s)
 {
     if (n < 0 || n > IC_MLP_NOALLOC_ROWS) throw std::invalid_argument("row count outside 0 .. IC_MLP_NOALLOC_ROWS");
     if (n == 0) return;
-    hipLaunchKernelGGL((k_infer<true>), infer_grid(n), dim3(NET_TH), 0, s, (const void *)raw, mean, std, params,
-                       (int)n, prob);
+    const uintptr_t p0 = (uintptr_t)prob, p1 = (uintptr_t)(prob + n);
+    auto on_prob = [&](const float *q, long count) { return (uintptr_t)q < p1 && (uintptr_t)(q + count) > p0; };
+    long r0 = n, r1 = n;                     // rows r0 .. r1 - 1 first
+    if (on_prob(params, IC_MLP_NPARAM) || on_prob(mean, IC_MLP_IN) || on_prob(std, IC_MLP_IN)) {
+        r0 = 0;
+    } else if (on_prob(raw, n * IC_MLP_IN)) {
+        const uintptr_t base = (uintptr_t)raw, row = IC_MLP_IN * sizeof(float);
+        r0 = p0 > base ? (long)((p0 - base) / row) : 0;
+        r1 = std::min(n, (long)((p1 - base + row - 1) / row));
+    }
+    if (r0 < r1)
+        hipLaunchKernelGGL((k_infer<true, true>), dim3(1), dim3(NET_TH), 0, s, (const void *)(raw + r0 * IC_MLP_IN), mean,
+                           std, params, (int)(r1 - r0), prob + r0);
+    for (const auto &part : {std::pair<long, long>{0, r0}, {r1, n}})
+        if (part.first < part.second)
+            hipLaunchKernelGGL((k_infer<true>), infer_grid(part.second - part.first), dim3(NET_TH), 0, s,
+                               (const void *)(raw + part.first * IC_MLP_IN), mean, std, params,
+                               (int)(part.second - part.first), prob + part.first);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) throw std::runtime_error(std::string("launch failed: ") + hipGetErrorString(e));
 }
