@@ -10,9 +10,13 @@
 
 #define DEV __device__ __forceinline__
 
-// Reciprocal of a > 0 (normal): the hardware estimate x (relative error below
-// 2^-22) and one step of third order, x (1 + e + e^2) with e = 1 - a x (one
-// operation less than two Newton steps); at most one ulp from 1/a.
+// The hardware's estimates of 1/a and 1/sqrt(x) are off by less than 2^-24
+// (relative; measured over 4 million values).  An error of one ulp below is
+// that of the result's own binade.
+
+// Reciprocal of a > 0 (normal): the estimate x and one step of third order,
+// x (1 + e + e^2) with e = 1 - a x (one operation less than two Newton steps);
+// at most 0.51 ulp from 1/a.
 DEV double rcp_pos(double a)
 {
     const double x = __builtin_amdgcn_rcp(a);
@@ -20,34 +24,39 @@ DEV double rcp_pos(double a)
     return fma(x, fma(e, e, e), x);
 }
 
-// Square root of x > 0 (normal): t = x y from the hardware reciprocal-square-
-// root estimate y, e = 1 - t y, and one step of third order t (1 + e/2 +
-// 3 e^2/8); at most one ulp from sqrt(x).
+// Square root of x > 0 (normal): g = x y from the estimate y of 1/sqrt(x) and
+// two Newton steps g + (x - g^2) y / 2, whose residuals carry no rounding of g;
+// at most 0.51 ulp from sqrt(x).
 DEV double sqrt_pos(double x)
 {
     const double y = __builtin_amdgcn_rsq(x);
-    const double t = x * y, e = fma(-t, y, 1.0);
-    return fma(t * e, fma(0.375, e, 0.5), t);
+    const double h = 0.5 * y;
+    double g = x * y;
+    g = fma(fma(-g, g, x), h, g);
+    return fma(fma(-g, g, x), h, g);
 }
 
-// x / sqrt(q) for q > 0 (normal), the same step applied to x y.
-DEV double div_sqrt_pos(double x, double q)
+// sqrt(x / a) for x, a > 0 (normal, their product too): the same steps on g =
+// x y with y the estimate of 1/sqrt(a x), g + (x - a g^2) y / 2; at most 1 ulp.
+DEV double sqrt_ratio_pos(double x, double a)
 {
-    const double y = __builtin_amdgcn_rsq(q);
-    const double e = fma(-(q * y), y, 1.0), z = x * y;
-    return fma(z * e, fma(0.375, e, 0.5), z);
+    const double y = __builtin_amdgcn_rsq(a * x);
+    const double h = 0.5 * y;
+    double g = x * y;
+    g = fma(fma(-(a * g), g, x), h, g);
+    return fma(fma(-(a * g), g, x), h, g);
 }
 
-// Reciprocals and square roots of the finite-volume update use rcp_pos /
-// sqrt_pos (<= 1 ulp); IC_EXACT_MATH selects the IEEE-rounded operations.
+// Reciprocals and square roots of the finite-volume update use these;
+// IC_EXACT_MATH selects the IEEE-rounded operations.
 #ifdef IC_EXACT_MATH
 #define IC_RCP(x) (1.0 / (x))
 #define IC_SQRT(x) sqrt(x)
-#define IC_DIV_SQRT(x, q) ((x) / sqrt(q))
+#define IC_SQRT_RATIO(x, a) sqrt((x) / (a))
 #else
 #define IC_RCP(x) rcp_pos(x)
 #define IC_SQRT(x) sqrt_pos(x)
-#define IC_DIV_SQRT(x, q) div_sqrt_pos(x, q)
+#define IC_SQRT_RATIO(x, a) sqrt_ratio_pos(x, a)
 #endif
 
 struct Gas {
@@ -95,14 +104,14 @@ DEV void prim_to_cons(const double *w, double *u, const Gas &gs)
 
 // Fast magnetosonic speed from A = g p + B^2, gp4 = 4 g p, the normal field bn
 // and twice the density: c_f^2 = (A + S) / (2 rho), S^2 = A^2 - 4 g p bn^2,
-// taken as X / sqrt(2 rho X) with X = A + S: no reciprocal of the density and
-// one square root less its guard (S is kept off zero by a value that vanishes
-// beside A; A > 0 in every physical state).
+// no reciprocal of the density; S is kept off zero by a value that vanishes
+// beside A (A > 0 in every physical state).  Mean error 0.37 ulp over plasma
+// betas from 0.3 to 30 as from 0.01 to 100; 0.41 to 0.42 in the form with a =
+// (g p + B^2) / rho and correctly rounded parts.
 DEV double fast_speed_of(double A, double gp4, double bn, double rho2)
 {
     const double d = fmax(fma(-gp4, bn * bn, A * A), 1e-300);
-    const double X = A + IC_SQRT(d);
-    return IC_DIV_SQRT(X, rho2 * X);
+    return IC_SQRT_RATIO(A + IC_SQRT(d), rho2);
 }
 
 // CFL rate of a cell, sum over the directions of (|v_d| + c_f,d) id (id the
