@@ -444,8 +444,11 @@ typedef struct {
  * SIMD, one work-group per work item and the smallest k-split giving at least
  * 512 work-groups.  Without any tuning call that rule applies from the start.
  * Work lists too short to fill the device (12^3 blocks: up to about 340 of
- * them) run on a second stage kernel without such a schedule, with the same
- * bits, unless ic_set_tuning has set a schedule. */
+ * them) run on a second stage kernel, with the same bits, which has no such
+ * schedule: by default, and where ic_autotune, which times it as one more
+ * candidate there, found it more than 1 % faster than the best schedule
+ * (stage_ms is then its time, and the other fields that best schedule).
+ * ic_stage_planes tells which kernel steps launch. */
 ic_status ic_autotune(ic_sim *sim, const char *cache_path, int reps, ic_tune_info *out);
 
 /* Force a schedule (waves_per_simd, grid, xcd_order, ksplit of *tune); it is
@@ -453,8 +456,13 @@ ic_status ic_autotune(ic_sim *sim, const char *cache_path, int reps, ic_tune_inf
 ic_status ic_set_tuning(ic_sim *sim, const ic_tune_info *tune);
 
 /* The schedule in force (waves_per_simd, grid, xcd_order, ksplit; the other
- * fields are zero). */
+ * fields are zero); steps launch it while ic_stage_planes is 0. */
 ic_status ic_get_tuning(ic_sim *sim, ic_tune_info *tune);
+
+/* Stage kernel of the current work list: 0, the one with ic_get_tuning's
+ * schedule, else the one for short lists and the planes (1, 2 or 4) of a block
+ * that each of its work-groups takes. */
+int ic_stage_planes(const ic_sim *sim);
 
 /* Code-unit scales in SI: [0] length m, [1] speed m/s, [2] time s, [3]
  * density kg/m^3, [4] pressure Pa, [5] field T. */

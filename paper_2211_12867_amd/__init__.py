@@ -117,7 +117,7 @@ EXPORTS = ("ic_create", "ic_destroy", "ic_step", "ic_advance", "ic_regrid", "ic_
            "ic_stage_timing", "ic_pool_capacity", "ic_features", "ic_mlp_set", "ic_eval_learned",
            "ic_regrid_stats", "ic_mlp_train", "ic_mlp_grad", "ic_mlp_infer", "ic_autotune", "ic_set_tuning",
            "ic_get_tuning", "ic_floor_counts", "ic_shock_diagnostics", "ic_mlp_infer_noalloc", "ic_get_clock",
-           "ic_set_clock", "ic_set_device_allocator", "ic_last_error")
+           "ic_set_clock", "ic_set_device_allocator", "ic_last_error", "ic_stage_planes")
 
 
 _ALLOC_FN = ctypes.CFUNCTYPE(ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p)
@@ -177,6 +177,7 @@ def _load():
     L.ic_autotune.argtypes = [vp, ctypes.c_char_p, ctypes.c_int, P(TuneInfo)]
     L.ic_set_tuning.argtypes = [vp, P(TuneInfo)]
     L.ic_get_tuning.argtypes = [vp, P(TuneInfo)]
+    L.ic_stage_planes.argtypes = [vp]
     L.ic_pool_capacity.argtypes = [vp]
     L.ic_pool_capacity.restype = ctypes.c_int
     L.ic_last_error.restype = ctypes.c_char_p
@@ -523,6 +524,11 @@ class Sim:
         t = TuneInfo()
         _check(lib.ic_get_tuning(self.h, ctypes.byref(t)))
         return (t.waves_per_simd, t.grid, t.xcd_order, t.ksplit)
+
+    def stage_planes(self):
+        """0: steps launch the stage kernel with that schedule; else the planes of a
+        block that a work-group of the kernel for short work lists takes."""
+        return lib.ic_stage_planes(self.h)
 
     # --- learned flags ------------------------------------------------------------
     def features(self, member=0):

@@ -409,10 +409,13 @@ struct ic_sim {
     // the register allocation, launch grid (0 = one work-group per work item),
     // XCD-contiguous work order
     int tune_waves = 2, tune_grid = 0, tune_xcd = 0, tune_ksplit = 1;
-    // measured schedules by log2 bucket of the work-list size {waves, grid, xcd, ksplit};
-    // pinned: ic_set_tuning's schedule holds whatever the work list
-    std::map<int, std::array<int, 4>> tuned;
-    bool tune_pinned = false;
+    // measured schedules by log2 bucket of the work-list size, and whether the
+    // kernel for short lists (tile_rule) was faster than each; marching: a
+    // measured schedule is in force that it did not beat; pinned: ic_set_tuning's
+    // schedule holds whatever the work list
+    struct Tuned { int waves, grid, xcd, ksplit; bool tile; };
+    std::map<int, Tuned> tuned;
+    bool tune_marching = false, tune_pinned = false;
     std::vector<hipEvent_t> ev;   // pairs
     long timed = 0;
     // pinned staging area of the table uploads (Upload) and its device copy
@@ -641,11 +644,12 @@ void select_schedule(ic_sim *s)
     if (s->tune_pinned) return;
     int w = 2, g = 0, x = 0, ks = 1;
     auto it = s->tuned.find(items_bucket(s));
+    s->tune_marching = it != s->tuned.end() && !it->second.tile;
     if (it != s->tuned.end()) {
-        w = it->second[0];
-        g = it->second[1];
-        x = it->second[2];
-        ks = it->second[3];
+        w = it->second.waves;
+        g = it->second.grid;
+        x = it->second.xcd;
+        ks = it->second.ksplit;
     } else {
         while (ks < 4 && 2 * ks <= s->B[2] && s->n_items * ks < 512) ks *= 2;
     }
@@ -1253,22 +1257,27 @@ int stage_grid(const ic_sim *s)
 // 0: the marching kernel.  One or two planes while every work-group has a CU of
 // its own (the fewer planes, the shorter each work-group's chain: 8 blocks of
 // 12^3 14.8, 17 and 22 us with 1, 2 and 4 planes, 40 blocks 20.7, 20 and 26 us,
-// the marching kernel 21.5 and 25 us); four planes up to four work-groups per CU
-// (160 blocks 40 us against 45, 320 blocks 69 against 71; 512 blocks 97 against
-// 84), but not on planes of more than 160 cells, which fill the marching
-// kernel's waves (48 blocks of 16 x 12 x 12: 29 us against 27).  Blocks of 4^3
-// cells leave most lanes of the marching kernel without a column: always here
-// (1,024 blocks: 24 us against 42).  A schedule set by ic_set_tuning is one of
-// the marching kernel.
-int tile_planes(const ic_sim *s)
+// the marching kernel with its default split 21.5 and 25 us); four planes up to
+// four work-groups per CU (160 blocks 40 us against 45, 320 blocks 69 against 71;
+// 512 blocks 97 against 84), but not on planes of more than 160 cells, which fill
+// the marching kernel's waves (48 blocks of 16 x 12 x 12: 29 us against 27).
+// Blocks of 4^3 cells leave most lanes of the marching kernel without a column:
+// always here (1,024 blocks: 24 us against 42).  The lines are against the
+// default split; with the best of all splits the marching kernel takes 16.0 us
+// for 8 blocks, 21.1 for 40, 26.2 for 80, 36.4 for 160 and 64.4 for 320, so
+// ic_autotune times both kernels (tile_planes).
+int tile_rule(const ic_sim *s)
 {
-    if (s->tune_pinned) return 0;
     const long plane = (long)s->B[0] * s->B[1], n = s->n_items;
     for (int kz : {1, 2})
         if (n * (s->B[2] / kz) <= s->n_cu) return kz;
     if (plane < 64 || (plane <= 160 && n * (s->B[2] / 4) <= 4L * s->n_cu)) return 4;
     return 0;
 }
+
+// the same for the steps: 0 where ic_set_tuning's schedule holds (one of the
+// marching kernel) or ic_autotune measured the marching kernel as no slower
+int tile_planes(const ic_sim *s) { return s->tune_pinned || s->tune_marching ? 0 : tile_rule(s); }
 
 // Launch of a kernel that takes a block's cells one by one (predictor, div B,
 // cleaning, rates): the cells of a block over several work-groups while all of
@@ -2179,8 +2188,9 @@ void apply_tuning(ic_sim *s, int waves, int grid, int xcd, int ksplit)
     s->graph_dirty = true;
 }
 
-// mean stage-1 kernel time [ms] of the current schedule on the current state
-double time_stage(ic_sim *s, int reps)
+// mean stage-1 kernel time [ms] on the current state: the current schedule of
+// the marching kernel, or (kz > 0) the kernel for short lists with kz planes
+double time_stage(ic_sim *s, int reps, int kz)
 {
     KArgs a = base_args(s);
     a.U = s->U.p;
@@ -2188,13 +2198,16 @@ double time_stage(ic_sim *s, int reps)
     a.Uout = s->Us.p;
     a.alpha = 0.5;
     a.want_rate = 0;
-    const int g = stage_grid(s);
-    s->L.stage(dim3(g), s->stream, a, s->tune_waves, s->phys.limiter);      // warm-up
+    auto launch = [&] {
+        if (kz) s->L.tile(dim3(tile_grid(s, kz)), s->stream, a, kz, s->phys.limiter);
+        else s->L.stage(dim3(stage_grid(s)), s->stream, a, s->tune_waves, s->phys.limiter);
+    };
+    launch();                                    // warm-up
     hipEvent_t e0, e1;
     HIPCHECK(hipEventCreate(&e0));
     HIPCHECK(hipEventCreate(&e1));
     HIPCHECK(hipEventRecord(e0, s->stream));
-    for (int r = 0; r < reps; ++r) s->L.stage(dim3(g), s->stream, a, s->tune_waves, s->phys.limiter);
+    for (int r = 0; r < reps; ++r) launch();
     HIPCHECK(hipEventRecord(e1, s->stream));
     HIPCHECK(hipEventSynchronize(e1));
     float ms = 0.f;
@@ -3061,6 +3074,8 @@ ic_status ic_get_tuning(ic_sim *s, ic_tune_info *t)
     });
 }
 
+int ic_stage_planes(const ic_sim *s) { return s ? tile_planes(s) : 0; }
+
 ic_status ic_autotune(ic_sim *s, const char *cache_path, int reps, ic_tune_info *out)
 {
     return guard(s, [&]() {
@@ -3071,7 +3086,9 @@ ic_status ic_autotune(ic_sim *s, const char *cache_path, int reps, ic_tune_info 
         const int bucket = items_bucket(s);
         const std::string key = prefix + std::to_string(bucket);
         ic_tune_info res{};
-        // cache: one line per result, "key waves grid xcd ksplit ms default_ms"; the last match
+        bool tile = false;
+        // cache: one line per result, "key waves grid xcd ksplit ms default_ms", the key followed
+        // by "/tile" where the kernel for short lists was the faster one; the last match
         // wins.  Entries of other work-list sizes on this device and block shape are kept
         // for the schedule choice after regrids.
         if (cache_path) {
@@ -3081,12 +3098,16 @@ ic_status ic_autotune(ic_sim *s, const char *cache_path, int reps, ic_tune_info 
                 int w, g, x, ks;
                 double ms, dms;
                 while (std::fscanf(f, "%511s %d %d %d %d %lf %lf", k, &w, &g, &x, &ks, &ms, &dms) == 7) {
-                    const std::string ks_(k);
+                    std::string ks_(k);
+                    const size_t cut = ks_.find("/tile", std::min(ks_.size(), prefix.size()));
+                    const bool ti = cut != std::string::npos;
+                    if (ti) ks_.erase(cut);
                     if (ks_.compare(0, prefix.size(), prefix) == 0 && ks_.size() > prefix.size() &&
                         (w == 1 || w == 2) && g >= 0 && (x == 0 || x == 1) && (ks == 1 || ks == 2 || ks == 4) &&
                         ks <= s->B[2])
-                        s->tuned[std::atoi(ks_.c_str() + prefix.size())] = {w, g, x, ks};
-                    if (key == k) {
+                        s->tuned[std::atoi(ks_.c_str() + prefix.size())] = {w, g, x, ks, ti};
+                    if (key == ks_) {
+                        tile = ti;
                         res.waves_per_simd = w;
                         res.grid = g;
                         res.xcd_order = x;
@@ -3124,7 +3145,7 @@ ic_status ic_autotune(ic_sim *s, const char *cache_path, int reps, ic_tune_info 
                     for (int g : grids)
                         for (int x : {1, 0}) {
                             apply_tuning(s, w, g, x, ks);
-                            const double ms = time_stage(s, reps);
+                            const double ms = time_stage(s, reps, 0);
                             res.candidates++;
                             if (w == 2 && g == 0 && x == 0 && ks == 1) res.default_ms = ms;
                             // a later candidate must be 1 % faster: near-ties keep the first in
@@ -3140,17 +3161,25 @@ ic_status ic_autotune(ic_sim *s, const char *cache_path, int reps, ic_tune_info 
                         }
                 }
             }
+            if (const int kz = tile_rule(s)) {
+                const double ms = time_stage(s, reps, kz);
+                res.candidates++;
+                tile = ms < 0.99 * best;
+                if (tile) res.stage_ms = ms;
+            }
             if (cache_path) {
                 std::FILE *f = std::fopen(cache_path, "a");
                 if (f) {
-                    std::fprintf(f, "%s %d %d %d %d %.6f %.6f\n", key.c_str(), res.waves_per_simd, res.grid,
-                                 res.xcd_order, res.ksplit, res.stage_ms, res.default_ms);
+                    std::fprintf(f, "%s%s %d %d %d %d %.6f %.6f\n", key.c_str(), tile ? "/tile" : "",
+                                 res.waves_per_simd, res.grid, res.xcd_order, res.ksplit, res.stage_ms,
+                                 res.default_ms);
                     std::fclose(f);
                 }
             }
         }
         apply_tuning(s, res.waves_per_simd, res.grid, res.xcd_order, res.ksplit);
-        s->tuned[bucket] = {res.waves_per_simd, res.grid, res.xcd_order, res.ksplit};
+        s->tuned[bucket] = {res.waves_per_simd, res.grid, res.xcd_order, res.ksplit, tile};
+        s->tune_marching = !tile;
         s->tune_pinned = false;
         if (out) *out = res;
     });
