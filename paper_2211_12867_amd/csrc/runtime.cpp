@@ -835,7 +835,11 @@ struct Upload {
 // and fills about 5 GB/s).  2,400 blocks of 16x12x12 out (354 MB, fresh pages):
 // 49.7 -> 11.4 ms; 32 members' states out 88 -> 17 ms and in 33 -> 23; 8 blocks
 // of 12^3 out 0.12 -> 0.08.  The area belongs to the sim and holds no more than
-// 16 MB; where it cannot be had, a copy call a block.
+// 16 MB; where it cannot be had, a copy call a block.  The first exchange pays for
+// it (8 blocks 0.13 ms, then 0.07; 75 of them 0.52, then 0.48; in a process that
+// has pinned nothing yet up to 0.3 ms more).  It is replaced only by one of more
+// than twice its size -- a smaller one takes more parts: a forest growing from 11
+// to 284 blocks read at each of 40 sizes 46 -> 35 ms.
 constexpr size_t IO_HALF = 8u << 20;
 constexpr size_t IO_INLINE = 1u << 20;      // below this the calling thread copies (a pool run costs about 30 us)
 
@@ -854,30 +858,39 @@ struct StateIO {
     int at_once = 0;            // blocks of a half
     size_t head = 0;            // the half's slot list, before its blocks
 
+    // a half of n blocks: their slots, then the blocks
+    size_t head_of(int n) const { return ((size_t)n * sizeof(int) + 255) / 256 * 256; }
+    size_t half_of(int n) const { return head_of(n) + n * bytes; }
+    int blocks_in(size_t half) const
+    {
+        int n = (int)(half / (bytes + sizeof(int)));
+        while (n > 0 && half_of(n) > half) --n;
+        return n;
+    }
+
     StateIO(ic_sim *s_, int n) : s(s_), per((size_t)s_->nv * s_->NC), bytes(per * sizeof(double))
     {
-        at_once = std::max(1, std::min(n, (int)(IO_HALF / bytes)));
-        head = ((size_t)at_once * sizeof(int) + 255) / 256 * 256;
-        const size_t half = head + (size_t)at_once * bytes;
-        for (hipEvent_t &e : s->io_done)
-            if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+        const size_t want = half_of(std::max(1, std::min(n, blocks_in(IO_HALF))));
+        if (want > 2 * s->hio_half) {
+            for (hipEvent_t &e : s->io_done)
+                if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+                    (void)hipGetLastError();
+                    e = nullptr;
+                    return;
+                }
+            char *area = nullptr;
+            if (hipHostMalloc((void **)&area, 2 * want) != hipSuccess) {
                 (void)hipGetLastError();
-                e = nullptr;
-                at_once = 0;
-                return;
+                if (!s->hio) return;
+            } else {
+                HIPCHECK(hipStreamSynchronize(s->stream));
+                if (s->hio) (void)hipHostFree(s->hio);
+                s->hio = area;
+                s->hio_half = want;
             }
-        if (half > s->hio_half) {
-            if (s->hio) HIPCHECK(hipHostFree(s->hio));
-            s->hio = nullptr;
-            s->hio_half = 0;
-            if (hipHostMalloc((void **)&s->hio, 2 * half) != hipSuccess) {
-                (void)hipGetLastError();
-                s->hio = nullptr;
-                at_once = 0;
-                return;
-            }
-            s->hio_half = half;
         }
+        at_once = std::max(1, std::min(n, blocks_in(s->hio_half)));
+        head = head_of(at_once);
     }
     char *half(int h) const { return s->hio + (size_t)h * s->hio_half; }
     // n bytes between the caller's array and a half, a megabyte a job
