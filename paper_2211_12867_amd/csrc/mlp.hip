@@ -820,18 +820,24 @@ void mlp_prob_flags(hipStream_t s, const float *prob, const int *items, int n, f
 
 // The buffers and launches of one forward and backward pass of n rows.
 struct Pass {
-    int n, nc, nz1, nz2;
+    int n = 0, nc = 0, nz1 = 0, nz2 = 0;
     Buf<uint16_t> wp, H1, dZ2, dZ1;
     Buf<float> loss, P1, P2, S;
     // Slices of the rows in the weight gradients: enough for about 256
     // work-groups a matrix, at most 32, each at least 4 MFMA steps.
     static int slices(int n, int tiles) { return std::max(1, std::min({32, (n + 31) / 32 / 4, (256 + tiles - 1) / tiles})); }
-    explicit Pass(int n_)
-        : n(n_), nc(std::max(1, std::min(64, n_ / 32))), nz1(slices(n_, 2 * IC_MLP_IN / 64)),
-          nz2(slices(n_, 2 * IC_MLP_HID / 64)), wp(PACK_N), H1((size_t)n_ * IC_MLP_HID), dZ2((size_t)n_ * IC_MLP_HID),
-          dZ1((size_t)n_ * IC_MLP_HID), loss(n_), P1((size_t)nz1 * IC_MLP_IN * IC_MLP_HID),
-          P2((size_t)nz2 * IC_MLP_HID * IC_MLP_HID), S((size_t)nc * SUMS)
+    void alloc(int rows)
     {
+        n = rows;
+        nc = std::max(1, std::min(64, n / 32));
+        nz1 = slices(n, 2 * IC_MLP_IN / 64);
+        nz2 = slices(n, 2 * IC_MLP_HID / 64);
+        wp.alloc(PACK_N);
+        for (Buf<uint16_t> *b : {&H1, &dZ2, &dZ1}) b->alloc((size_t)n * IC_MLP_HID);
+        loss.alloc(n);
+        P1.alloc((size_t)nz1 * IC_MLP_IN * IC_MLP_HID);
+        P2.alloc((size_t)nz2 * IC_MLP_HID * IC_MLP_HID);
+        S.alloc((size_t)nc * SUMS);
     }
     // the packed weights of the first pass; each Adam step then leaves the next one's
     void pack(hipStream_t s, const float *w)
@@ -871,7 +877,8 @@ void mlp_grad(const float *xnorm, const uint8_t *y, int n, float pw, const float
     Buf<uint16_t> xb((size_t)n * IC_MLP_IN);
     Buf<uint8_t> yd(n);
     Buf<double> lsum(1);
-    Pass pass(n);
+    Pass pass;
+    pass.alloc(n);
     if (hipMemcpy(x.p, xnorm, (size_t)n * IC_MLP_IN * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(w.p, params, IC_MLP_NPARAM * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(yd.p, y, n, hipMemcpyHostToDevice) != hipSuccess)
@@ -902,22 +909,32 @@ void mlp_train(const float *raw, const uint8_t *y, long n, const MlpHparams &hp,
     auto D2H = [](void *h, const void *d, size_t bytes) {
         if (hipMemcpy(h, d, bytes, hipMemcpyDeviceToHost) != hipSuccess) throw std::runtime_error("hipMemcpy failed");
     };
+    const int B = hp.batch;
+    const long nbatch = n / B;
     Buf<float> rawd((size_t)n * IC_MLP_IN), mean(IC_MLP_IN), istd(IC_MLP_IN), w(IC_MLP_NPARAM), m1(IC_MLP_NPARAM),
         m2(IC_MLP_NPARAM);
-    Buf<double> stat(2 * IC_MLP_IN);
+    Buf<double> stat(2 * IC_MLP_IN), lossacc;            // lossacc: per-minibatch loss sums, read once per epoch
+    Buf<uint16_t> xall, xb;
+    Buf<uint8_t> yall;
+    Buf<long> orderd;
+    Pass pass;
+    // the device is done with the buffers before any of them is given back, also
+    // where an allocation fails while the statistics run
+    struct Idle {
+        ~Idle() { (void)hipStreamSynchronize(nullptr); }
+    } idle;
     H2D(rawd.p, raw, (size_t)n * IC_MLP_IN * sizeof(float));
     // per-feature z-score statistics of the training set (fp64)
     hipLaunchKernelGGL((k_stats<true>), dim3(IC_MLP_IN / STAT_C), dim3(1024), 0, s, (const float *)rawd.p, n, stat.p,
                        stat.p + IC_MLP_IN);
     hipLaunchKernelGGL((k_stats<false>), dim3(IC_MLP_IN / STAT_C), dim3(1024), 0, s, (const float *)rawd.p, n, stat.p,
                        stat.p + IC_MLP_IN);
-    const int B = hp.batch;
-    const long nbatch = n / B;
-    Buf<uint16_t> xall((size_t)n * IC_MLP_IN), xb((size_t)B * IC_MLP_IN);
-    Buf<uint8_t> yall(n);
-    Buf<long> orderd(n);
-    Buf<double> lossacc(std::max(nbatch, 1L));           // per-minibatch loss sums, read once per epoch
-    Pass pass(B);
+    xall.alloc((size_t)n * IC_MLP_IN);
+    xb.alloc((size_t)B * IC_MLP_IN);
+    yall.alloc(n);
+    orderd.alloc(n);
+    lossacc.alloc(std::max(nbatch, 1L));
+    pass.alloc(B);
     long npos = 0;
     for (long b = 0; b < n; ++b) npos += y[b] ? 1 : 0;
     const float pw = hp.pos_weight > 0.f ? hp.pos_weight : (npos > 0 ? (float)(n - npos) / (float)npos : 1.f);
