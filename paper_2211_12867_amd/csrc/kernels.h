@@ -171,6 +171,9 @@ struct IndicatorParams {
     double tr_r, tr_c;                             // tracer fractions that refine / keep a block
 };
 
+// cells of a plane up to which the stage kernel for short lists takes four at once
+constexpr int TILE4_PLANE = 160;
+
 // Launch wrappers per block shape (kernels.hip, stage.hip); the runtime calls these.
 struct Launchers {
     void (*stage)(dim3, hipStream_t, const KArgs &, int waves, int limiter);

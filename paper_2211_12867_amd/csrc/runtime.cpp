@@ -1284,7 +1284,7 @@ int tile_rule(const ic_sim *s)
     const long plane = (long)s->B[0] * s->B[1], n = s->n_items;
     for (int kz : {1, 2})
         if (n * (s->B[2] / kz) <= s->n_cu) return kz;
-    if (plane < 64 || (plane <= 160 && n * (s->B[2] / 4) <= 4L * s->n_cu)) return 4;
+    if (plane < 64 || (plane <= TILE4_PLANE && n * (s->B[2] / 4) <= 4L * s->n_cu)) return 4;
     return 0;
 }
 

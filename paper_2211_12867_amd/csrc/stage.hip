@@ -838,13 +838,14 @@ void launch_stage(dim3 g, hipStream_t s, const KArgs &a, int waves, int limiter)
     }
 }
 
-// kz planes of a block per work-group: 1, 2 or 4
+// kz planes of a block per work-group: 1, 2 or, on planes of up to TILE4_PLANE
+// cells, 4
 template <int BI, int BJ, int BK, int NV, int LIM>
 void launch_tile_lim(dim3 g, hipStream_t s, const KArgs &a, int kz)
 {
     if (kz == 1) hipLaunchKernelGGL((k_tile<BI, BJ, BK, NV, LIM, 1>), g, dim3(TT), 0, s, a);
     else if (kz == 2) hipLaunchKernelGGL((k_tile<BI, BJ, BK, NV, LIM, 2>), g, dim3(TT), 0, s, a);
-    else hipLaunchKernelGGL((k_tile<BI, BJ, BK, NV, LIM, 4>), g, dim3(TT), 0, s, a);
+    else if constexpr (BI * BJ <= TILE4_PLANE) hipLaunchKernelGGL((k_tile<BI, BJ, BK, NV, LIM, 4>), g, dim3(TT), 0, s, a);
 }
 template <int BI, int BJ, int BK, int NV>
 void launch_tile(dim3 g, hipStream_t s, const KArgs &a, int kz, int limiter)
