@@ -58,10 +58,12 @@ def build(verbose=False, out=None, defines=(), extra=()):
     return target
 
 
-# Host code instrumented by AddressSanitizer and UndefinedBehaviorSanitizer,
-# device code as usual (every -fsanitize= goes to the host pass only)
+# Host code instrumented by AddressSanitizer and UndefinedBehaviorSanitizer at
+# -O1, device code as in the library (every -fsanitize= and the -O1 go to the
+# host pass only)
 SAN_HOST = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
             "-Xarch_host", "-fno-omit-frame-pointer", "-Xarch_host", "-fno-sanitize-recover=undefined"]
+SAN_FLAGS = FLAGS + ["-Xarch_host", "-O1", "-Xarch_host", "-g"] + SAN_HOST
 SAN_EXE = os.path.join(HERE, "icarus_san")
 
 
@@ -69,9 +71,8 @@ def build_sanitized(verbose=False):
     """The library's sources and csrc/sanitize_driver.cpp linked into one
     executable whose host code runs under the sanitizers (a driver program,
     not a Python extension: the sanitizer runtime is linked into it)."""
-    flags = [f for f in FLAGS if f != "-O3"] + ["-O1", "-g"] + SAN_HOST
-    jobs = [(os.path.join(CSRC, src), os.path.join(CSRC, src + ".san.o"), flags) for src in SOURCES]
-    jobs.append((os.path.join(CSRC, "sanitize_driver.cpp"), os.path.join(CSRC, "sanitize_driver.san.o"), flags))
+    jobs = [(os.path.join(CSRC, src), os.path.join(CSRC, src + ".san.o"), SAN_FLAGS) for src in SOURCES]
+    jobs.append((os.path.join(CSRC, "sanitize_driver.cpp"), os.path.join(CSRC, "sanitize_driver.san.o"), SAN_FLAGS))
     objs = _compile_all(jobs, verbose)
     tmp = SAN_EXE + ".tmp"
     cmd = ["hipcc", f"--offload-arch={ARCH}"] + SAN_HOST + ["-o", tmp] + objs
