@@ -47,6 +47,11 @@ __device__ inline float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h <<
 // a patch and variable adds the patch's cells in order.  With a thread a patch
 // that read its own cells (strided, 192 of 256 threads idle) the launches of
 // the level-5 run took 29 us, now 20.5; about 300 blocks 13.6 us, now 12.
+// On 4^3 blocks a patch is a cell: a lane takes one through, four blocks a
+// work-group (4,096 blocks 7.7 us, with a thread a patch over one block 8.9; by
+// layers through LDS 16,384 blocks took 58 us, a thread a patch 20).
+constexpr int FEATURE_BLOCKS = 4;
+
 template <int BI, int BJ, int BK>
 __global__ void __launch_bounds__(256) k_features(KArgs a, const int *items, const int *nitems_ptr, float *raw,
                                                   const float *mean, const float *istd, uint16_t *xb)
@@ -55,6 +60,24 @@ __global__ void __launch_bounds__(256) k_features(KArgs a, const int *items, con
     constexpr int PI = BI / 4, PJ = BJ / 4, PK = BK / 4, LC = BI * BJ * PK;      // cells of a layer
     __shared__ double sw[8][LC];
     const int n = *nitems_ptr, pk = blockIdx.y, t = threadIdx.x;
+    auto put = [&](int it, int idx, double m) {
+        if (idx < 64 || idx >> 6 == 4) m = log10(m);          // density and pressure
+        const float f = (float)m;
+        if (raw) raw[(size_t)it * IC_MLP_IN + idx] = f;
+        if (xb) xb[(size_t)it * IC_MLP_IN + idx] = f2bf((f - mean[idx]) * istd[idx]);
+    };
+    if constexpr (S::NC == 64) {
+        for (int it = blockIdx.x * FEATURE_BLOCKS + t / 64; it < n; it += gridDim.x * FEATURE_BLOCKS) {
+            const int slot = items[it], c = t % 64;
+            double u[8], w[8];
+#pragma unroll
+            for (int v = 0; v < 8; ++v) u[v] = a.U[((size_t)slot * a.nv + v) * S::NC + c];
+            cons_to_prim<true>(u, w, a.gas);
+#pragma unroll
+            for (int v = 0; v < 8; ++v) put(it, v * 64 + c, 0.0 + w[v]);
+        }
+        return;
+    }
     for (int it = blockIdx.x; it < n; it += gridDim.x) {
         const int slot = items[it];
         for (int c = t; c < LC; c += 256) {
@@ -75,12 +98,7 @@ __global__ void __launch_bounds__(256) k_features(KArgs a, const int *items, con
                 for (int j = 0; j < PJ; ++j)
 #pragma unroll
                     for (int i = 0; i < PI; ++i) sum += sw[v][pi * PI + i + BI * (pj * PJ + j + BJ * k)];
-            double m = sum * (1.0 / (PI * PJ * PK));
-            if (v == 0 || v == 4) m = log10(m);
-            const float f = (float)m;
-            const int idx = v * 64 + pk * 16 + (t & 15);
-            if (raw) raw[(size_t)it * IC_MLP_IN + idx] = f;
-            if (xb) xb[(size_t)it * IC_MLP_IN + idx] = f2bf((f - mean[idx]) * istd[idx]);
+            put(it, v * 64 + pk * 16 + (t & 15), sum * (1.0 / (PI * PJ * PK)));
         }
         __syncthreads();               // the cells are read before the next block's are written
     }
@@ -802,9 +820,10 @@ void MlpDevice::forward(hipStream_t s, int n)
 void mlp_features(hipStream_t s, const KArgs &a, int bi, int bj, int bk, const int *items,
                   const int *nitems, int n, float *raw, const float *mean, const float *istd, uint16_t *xb)
 {
-    const dim3 g(std::max(1, std::min(n, 16384)), 4);
 #define IC_INSTANTIATE(BI, BJ, BK)                                                                      \
     if (bi == BI && bj == BJ && bk == BK) {                                                            \
+        const dim3 g = BI * BJ * BK == 64 ? dim3(std::max(1, (n + FEATURE_BLOCKS - 1) / FEATURE_BLOCKS))  \
+                                          : dim3(std::max(1, std::min(n, 16384)), 4);                   \
         hipLaunchKernelGGL((k_features<BI, BJ, BK>), g, dim3(256), 0, s, a, items, nitems, raw, mean,   \
                            istd, xb);                                                                   \
         return;                                                                                        \
