@@ -27,7 +27,9 @@
 // fast speed), the passes spread over the four waves so that no SIMD carries
 // more than another (PassSplit), one barrier a plane (two planes of primitives
 // and of differences in LDS), loads into registers a plane ahead, LDS rows
-// pitched against bank conflicts, nothing spilled in the plane loop.
+// pitched against bank conflicts, nothing spilled in the plane loop with eight
+// variables (up to nine registers once per work item; with the tracer up to 24,
+// and six scratch accesses a plane).
 // Measured on 512 x 60 x 180 cells (2,400 blocks of 16 x 12 x 12): 403 us a
 // launch, before 484 us; 4,096 blocks of 12^3: 543 us (13.0 G cells/s); 8 blocks
 // of 12^3, one work-group each: 52 us, before 71 us (a wave without columns did
@@ -663,11 +665,13 @@ k_stage(KArgs a)
 // in LDS, the phi ones behind a barrier, and after another one every thread
 // updates cells.  It executes about 1.3 times the instructions (the phi rows of
 // KZ cells carry four halo cells), but no wave waits for another's plane, and
-// four waves a SIMD (128 VGPRs) hide each other's latency.
+// four waves a SIMD hide each other's latency (128 VGPRs: up to 19 values are
+// spilled and read back once per work item, none in the passes' loops).
 
-// Measured (stage launch, k_stage with its default schedule / k_tile): 8 blocks
-// of 12^3 21.5 / 14.8 us, 40 of them 25 / 20, 80 31 / 26, 160 45 / 40, 320 71 /
-// 69, 512 84 / 97; 1,024 blocks of 4^3 42 / 24; 48 of 16 x 12 x 12 27 / 29.
+// Measured (stage launch, k_stage with its default split, with its best one,
+// k_tile): 8 blocks of 12^3 21.5, 16.0, 14.8 us, 40 of them 25, 21.1, 20, 80 31,
+// 26.2, 26, 160 45, 36.4, 40, 320 71, 64.4, 69, 512 84, 84.2, 97; 1,024 blocks of
+// 4^3 42 and 24 (default, k_tile), 48 of 16 x 12 x 12 27 and 29.
 constexpr int TT = 512;      // threads per work-group of k_tile
 
 // Rows along D of planes k0 .. k0 + KZ - 1, and how many go into a pass.

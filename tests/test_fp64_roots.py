@@ -2,13 +2,12 @@
 compiled for the host, the hardware's estimates stood in by values off by up to
 2^-24, their measured bound), against 113-bit arithmetic (CPU only).
 
-Bounds in ulps.  A Newton step on an estimate off by e leaves e^2 / 2; after two
-(sqrt_pos, sqrt_ratio_pos; the third-order one of rcp_pos leaves e^3) that is
-below 2^-90, so what counts is the rounding of the last operation, 1/2, and for
-the ratio the product a g in its residual: 2^-53 of it moves g by 2^-54 of
-itself, another 1/2 at most.  The fast speed is to be no further off than in the
-form with the squared speeds divided by the density, from correctly rounded
-parts."""
+Bounds in ulps.  After two Newton steps on an estimate off by e = 2^-24 (sqrt_pos;
+their residuals carry no rounding of the iterate) or one third-order step (e^3 is
+left) what counts is roundings: the last operation's, 1/2, and for sqrt_ratio_pos
+half of those of g and a g, together 2^-53 of the result, another ulp at most.
+The fast speed is to be no further off than in the form with the squared speeds
+divided by the density, from correctly rounded parts."""
 import os
 import shutil
 import subprocess
@@ -93,6 +92,6 @@ def test_roots_and_fast_speed(tmp_path):
     r = {k: (float(a), float(b)) for k, a, b in
          (line.split() for line in subprocess.check_output([exe], text=True).splitlines())}
     print(r)
-    assert r["rcp"][0] < 0.51 and r["sqrt"][0] < 0.51 and r["ratio"][0] < 1.01
+    assert r["rcp"][0] < 0.51 and r["sqrt"][0] < 0.51 and r["ratio"][0] < 1.51
     for k in ("", "_wide"):
         assert r["speed" + k][1] <= r["squared" + k][1]
