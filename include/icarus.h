@@ -396,8 +396,8 @@ ic_status ic_mlp_infer(const float *raw, long n, const float *params, const floa
  * returns without synchronising; prob_dev is valid once the stream has
  * completed it.  n may not exceed IC_MLP_NOALLOC_ROWS (IC_E_INVALID).  Kernel
  * launches alone (one, unless prob_dev lies on inputs); calls share no memory
- * of the library, so calls on other streams or threads may overlap.  Results equal ic_mlp_infer's bit for
- * bit. */
+ * of the library, so calls on other streams or threads may overlap.  Results
+ * equal ic_mlp_infer's bit for bit. */
 #define IC_MLP_NOALLOC_ROWS 4096
 ic_status ic_mlp_infer_noalloc(const float *raw_dev, long n, const float *params_dev, const float *mean_dev,
                                const float *std_dev, float *prob_dev, void *hip_stream);
@@ -481,8 +481,8 @@ int ic_pool_capacity(const ic_sim *sim);
  * least 256 bytes, or NULL (the allocating call then fails with IC_E_NOMEM).
  * Every buffer goes back through the allocator it came from, also after a
  * later change.  Pinned host memory is not affected.  Process-wide: do not
- * call it while another thread is inside the library.  IC_E_INVALID if exactly one of alloc
- * and release is NULL. */
+ * call it while another thread is inside the library.  IC_E_INVALID if exactly
+ * one of alloc and release is NULL. */
 typedef void *(*ic_alloc_fn)(size_t bytes, void *user);
 typedef void (*ic_free_fn)(void *ptr, void *user);
 ic_status ic_set_device_allocator(ic_alloc_fn alloc, ic_free_fn release, void *user);

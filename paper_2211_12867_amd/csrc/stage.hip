@@ -31,9 +31,10 @@
 // variables (up to nine registers once per work item; with the tracer up to 24,
 // and six scratch accesses a plane).
 // Measured on 512 x 60 x 180 cells (2,400 blocks of 16 x 12 x 12): 403 us a
-// launch, before 484 us; 4,096 blocks of 12^3: 543 us (13.0 G cells/s); 8 blocks
-// of 12^3, one work-group each: 52 us, before 71 us (a wave without columns did
-// nothing in the face phases of 12 x 12 planes).
+// launch (in XCD-contiguous order 390 to 410 on several cards), before 484 us;
+// 4,096 blocks of 12^3: 543 to 559 us (13 G cells/s); 8 blocks of 12^3, one
+// work-group each: 52 us, before 71 us (a wave without columns did nothing in the
+// face phases of 12 x 12 planes).
 #include "common.h"
 
 // ---------------------------------------------------------------------------
